@@ -16,7 +16,8 @@ INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "librr.so")
 BUILD = os.path.join(HERE, "_build")
 
-SOURCES = ["rr_api.cpp", "rr_build.cpp", "rr_tune.cpp", "rr_server.cpp", "rr_kernels.hip", "rr_scan.hip", "rr_probe.hip"]
+SOURCES = ["rr_api.cpp", "rr_build.cpp", "rr_tune.cpp", "rr_server.cpp", "rr_kernels.hip", "rr_scan.hip", "rr_scan_f32.hip",
+           "rr_probe.hip"]
 # rr_inst.hip holds the search kernels of one kernel data type (element type
 # u8 0, i8 1, f32 2, bf16 pass 3, 8-bit pass 4; + 8 for the inner product);
 # it is compiled once per type so the instantiations build in parallel.
@@ -28,9 +29,9 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "-I", CSRC, "-Wall",
           "-Wno-unused-function", "-Wno-unused-variable", "-Xarch_host", "-march=x86-64-v3"]
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-munsafe-fp-atomics"]
-# The MFMA scan keeps its accumulators in ordinary VGPRs, so that the
+# The MFMA scans keep their accumulators in ordinary VGPRs, so that the
 # per-element epilogue reads them without accumulator-register moves.
-PER_SOURCE = {"rr_scan.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+PER_SOURCE = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("rr_scan.hip", "rr_scan_f32.hip")}
 
 
 def _compile(src: str) -> str:

@@ -382,7 +382,8 @@ static void free_device(rr_index *ix) {
     ix->alloc.release(ix->d_adj);
     ix->alloc.release(ix->d_sq8);
     ix->alloc.release(ix->d_deg);
-    ix->d_base = ix->d_bf16 = ix->d_adj = ix->d_sq8 = ix->d_deg = nullptr;
+    ix->alloc.release(ix->d_norm);
+    ix->d_base = ix->d_bf16 = ix->d_adj = ix->d_sq8 = ix->d_deg = ix->d_norm = nullptr;
     ix->on_device = false;
     if (cur >= 0) (void)hipSetDevice(cur);
 }
@@ -423,6 +424,7 @@ extern "C" rr_status rr_index_to_device(rr_index *ix, const rr_allocator *alloc,
     if (ix->dtype == RR_F32) {
         rb16 = padded_row_bytes((int64_t)ix->d * 2);
         std::vector<uint16_t> h((size_t)ix->n * (rb16 / 2), 0);
+        std::vector<float> hn((size_t)ix->n);
         const float *x = (const float *)ix->base.data();
         for (int64_t i = 0; i < ix->n; ++i) {
             double nn = 0;
@@ -432,7 +434,12 @@ extern "C" rr_status rr_index_to_device(rr_index *ix, const rr_allocator *alloc,
                 nn += (double)v * v;
             }
             maxn = std::max(maxn, (float)std::sqrt(nn));
+            hn[(size_t)i] = (float)(0.5 * nn);
         }
+        ix->d_norm = ix->alloc.alloc(hn.size() * sizeof(float));
+        if (!ix->d_norm) return fail(RR_ENOMEM, "device allocation failed");
+        HIP_TRY(hipMemcpyAsync(ix->d_norm, hn.data(), hn.size() * sizeof(float), hipMemcpyHostToDevice, s));
+        HIP_TRY(hipStreamSynchronize(s));
         ix->d_bf16 = ix->alloc.alloc(h.size() * 2);
         if (!ix->d_bf16) return fail(RR_ENOMEM, "device allocation failed");
         HIP_TRY(hipMemcpyAsync(ix->d_bf16, h.data(), h.size() * 2, hipMemcpyHostToDevice, s));
@@ -498,6 +505,7 @@ extern "C" rr_status rr_index_to_device(rr_index *ix, const rr_allocator *alloc,
     dv.adj = (const int32_t *)ix->d_adj;
     dv.deg = (const uint8_t *)ix->d_deg;
     dv.max_norm = maxn;
+    dv.half_norm = (const float *)ix->d_norm;
     dv.base_sq8 = (const uint8_t *)ix->d_sq8;
     dv.row_bytes_sq8 = rb8;
     dv.sq_lo = sq_lo;
@@ -1074,7 +1082,7 @@ static rr_status brute_force_once(const rr_index *ix, const void *queries_dev, i
     const int64_t item_cap = std::max<int64_t>(cap, 1);
     rr_results *res = nullptr;
     rr_status st = make_results(ix, ix->dev, nq, &sp, true, item_cap, item_cap, 1024,
-                                ix->dev.row_bytes, alloc, stream, &res);
+                                ix->dev.row_bytes + (int32_t)scan_ws_row(ix->dev), alloc, stream, &res);
     if (st != RR_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     SearchBufs &sb = res->sb;
@@ -1095,7 +1103,9 @@ static rr_status brute_force_once(const rr_index *ix, const void *queries_dev, i
     HIP_TRY_R(launch_fill_u64(sb.counters, CTR_COUNT, 0ull, s));
     HIP_TRY_R(launch_fill_u64(sb.level_cnt, sb.max_levels, 0ull, s));
     HIP_TRY_R(launch_prep_queries(ix->dev, queries_dev, nq, radius, radius_dev, cfg, sb, s));
-    HIP_TRY_R(launch_brute_force(ix->dev, sb.qpad, sb.qth, nq, sb, device_cus(), s));
+    // the scan's scratch follows the padded queries
+    HIP_TRY_R(launch_brute_force(ix->dev, sb.qpad, sb.qth, nq, sb, sb.qpad + nq * ix->dev.row_bytes,
+                                 device_cus(), s));
     // the hit count decides whether the capacity sufficed (ground truth is
     // not on a timed path, so this call synchronizes)
     unsigned long long h = 0;
@@ -1283,7 +1293,8 @@ extern "C" rr_status rr_nn_dist(const rr_index *ix, const void *queries_dev, int
     hipStream_t s = (hipStream_t)stream;
     rr::Allocator al = ix->alloc;
     al.stream = stream;
-    const size_t qbytes = (size_t)nq * ix->dev.row_bytes;
+    const size_t qrows = (size_t)nq * ix->dev.row_bytes;
+    const size_t qbytes = qrows + (size_t)nq * scan_ws_row(ix->dev); // the scan's scratch follows
     const size_t tbytes = ((qbytes + 255) & ~(size_t)255) + (size_t)nq * (sizeof(QThresh) + 8) + 512;
     uint8_t *tmp = (uint8_t *)al.alloc(tbytes);
     if (!tmp) return fail(RR_ENOMEM, "device allocation failed");
@@ -1294,7 +1305,7 @@ extern "C" rr_status rr_nn_dist(const rr_index *ix, const void *queries_dev, int
         (unsigned long long *)((uint8_t *)sb.qth + (((size_t)nq * sizeof(QThresh) + 255) & ~(size_t)255));
     SearchCfg cfg{};
     hipError_t e = launch_prep_queries(ix->dev, queries_dev, nq, 0.0, nullptr, cfg, sb, s);
-    if (e == hipSuccess) e = launch_nn_dist(ix->dev, sb.qpad, nq, nn_dev, bits, s);
+    if (e == hipSuccess) e = launch_nn_dist(ix->dev, sb.qpad, nq, nn_dev, bits, tmp + qrows, s);
     if (e == hipSuccess && !al.has_user) e = hipStreamSynchronize(s);
     al.release(tmp);
     if (e != hipSuccess) return fail(RR_EHIP, "nn_dist: %s", hipGetErrorString(e));

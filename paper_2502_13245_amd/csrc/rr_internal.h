@@ -47,6 +47,7 @@ struct DevIndex {
     const int32_t *adj = nullptr;
     const uint8_t *deg = nullptr; // [n] out-degree of every point
     float max_norm = 0.f; // largest |x| (float data)
+    const float *half_norm = nullptr; // [n] |x|^2 / 2 rounded to float32 (float data)
     int32_t metric = 0;   // rr_metric
     int64_t key_off = 0;  // integer data, inner product: keys are key_off - <p, q>
     const uint8_t *base_sq8 = nullptr; // float data: 8-bit codes, x ~ sq_lo + sq_scale * code
@@ -225,15 +226,16 @@ hipError_t launch_results_copy(int dtype, int precision, const DevIndex &ix, con
                                int64_t capacity = INT64_MAX, bool scan_counts = true);
 size_t results_copy_tmp_bytes(int64_t nq);
 
-// brute force (rr_scan.hip)
+// brute force (rr_scan.hip); ws: scan_ws_row(ix) bytes of scratch per query
+int64_t scan_ws_row(const DevIndex &ix);
 hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth,
-                              int64_t nq, SearchBufs &sb, int num_cus, hipStream_t s);
+                              int64_t nq, SearchBufs &sb, uint8_t *ws, int num_cus, hipStream_t s);
 // memory-system probe (rr_probe.hip): partial sums written, and the launch
 int64_t probe_parts(int64_t gathers);
 hipError_t launch_probe_rows(const DevIndex &ix, int64_t gathers, uint64_t seed, unsigned long long *sink,
                              hipStream_t s);
 hipError_t launch_nn_dist(const DevIndex &ix, const uint8_t *qpad, int64_t nq, double *nn,
-                          unsigned long long *bits, hipStream_t s);
+                          unsigned long long *bits, uint8_t *ws, hipStream_t s);
 hipError_t launch_finalize(int dtype, SearchBufs &sb, int num_cus, hipStream_t s);
 // radix select: hist[256] = counts of the 8-bit digit at `shift` among the
 // keys (uint32, or FP64 mapped to ordered uint64) whose masked bits equal prefix
@@ -266,7 +268,8 @@ struct rr_index {
     bool on_device = false;
     int device = -1;
     rr::Allocator alloc;
-    void *d_base = nullptr, *d_bf16 = nullptr, *d_adj = nullptr, *d_sq8 = nullptr, *d_deg = nullptr;
+    void *d_base = nullptr, *d_bf16 = nullptr, *d_adj = nullptr, *d_sq8 = nullptr, *d_deg = nullptr,
+         *d_norm = nullptr;
     rr::DevIndex dev;
 };
 

@@ -1,0 +1,48 @@
+// rr_scan.h -- what the dense scans of rr_scan.hip and rr_scan_f32.hip share.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "rr_internal.h"
+
+namespace rr {
+
+enum { SCAN_NN = 0, SCAN_RANGE = 1 };
+
+struct ScanArgs {
+    DevIndex ix;
+    const uint8_t *qpad;  // [nq][row_bytes]
+    const QThresh *qth;   // [nq] (range mode)
+    int64_t nq;
+    int64_t chunk;        // base points per workgroup
+    // nn mode
+    unsigned long long *nn_bits; // [nq] min distance bits (uint32 value or double bits)
+    // range mode: hits appended as items (task = query)
+    unsigned long long *item_key; // (query << 32) | id
+    void *item_dist;
+    int64_t item_cap;
+    unsigned long long *item_cursor;
+    unsigned long long *task_cnt;
+    unsigned long long *overflow;
+};
+
+// order-preserving map of a double to an unsigned key (atomicMin over
+// signed distances) and back
+__device__ __forceinline__ unsigned long long dbl_order(double d) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(d);
+    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+__device__ __forceinline__ double dbl_unorder(unsigned long long k) {
+    return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
+}
+
+// rr_scan_f32.hip: whether the split-bfloat16 scan takes this index, and its
+// two scans (ws: scan_ws_row bytes per query)
+bool scan_split_ok(const DevIndex &ix);
+hipError_t launch_split_range(const ScanArgs &a, uint8_t *ws, hipStream_t s);
+// writes nn_bits (dbl_order of the smallest distance of every query)
+hipError_t launch_split_nn(const ScanArgs &a, uint8_t *ws, hipStream_t s);
+
+} // namespace rr

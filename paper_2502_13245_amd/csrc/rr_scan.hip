@@ -6,7 +6,9 @@
 //  * uint8 / int8: v_mfma_i32_16x16x64_i8.  uint8 values are shifted by -128
 //    (x ^ 0x80) into int8; squared distances are shift invariant, so
 //    d = |q'|^2 + |x'|^2 - 2 q'.x' is exact in int32.
-//  * float32: v_mfma_f64_16x16x4f64 on the float32 values widened to FP64,
+//  * float32: a bfloat16 filter with an exact FP64 decision
+//    (rr_scan_f32.hip); data whose squares leave the float32 range takes
+//    k_scan_f32 here, v_mfma_f64_16x16x4f64 on the values widened to FP64,
 //    d = |q|^2 + |x|^2 - 2 q.x in FP64.
 // The negated inner product (Section 2) uses the same products: float32
 // d = -q.x; integer data keeps the search's unsigned key key_off - q.x,
@@ -23,31 +25,12 @@
 #include <climits>
 #include <cstdint>
 
-#include "rr_internal.h"
+#include "rr_scan.h"
 
 namespace rr {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
-
-enum { SCAN_NN = 0, SCAN_RANGE = 1 };
-
-struct ScanArgs {
-    DevIndex ix;
-    const uint8_t *qpad;  // [nq][row_bytes]
-    const QThresh *qth;   // [nq] (range mode)
-    int64_t nq;
-    int64_t chunk;        // base points per workgroup
-    // nn mode
-    unsigned long long *nn_bits; // [nq] min distance bits (uint32 value or double bits)
-    // range mode: hits appended as items (task = query)
-    unsigned long long *item_key; // (query << 32) | id
-    void *item_dist;
-    int64_t item_cap;
-    unsigned long long *item_cursor;
-    unsigned long long *task_cnt;
-    unsigned long long *overflow;
-};
 
 // 16-query tiles per wave: 8 for rows up to 128 bytes (twice the MFMA work
 // per base tile loaded), 4 for longer rows, whose A operands would not fit
@@ -100,16 +83,6 @@ __device__ __forceinline__ int row_sum_u8(uint4 v, int s) {
     t = __builtin_amdgcn_udot4(v.z, 0x01010101u, t, false);
     t = __builtin_amdgcn_udot4(v.w, 0x01010101u, t, false);
     return (int)t;
-}
-
-// order-preserving map of a double to an unsigned key (atomicMin over
-// signed distances) and back
-__device__ __forceinline__ unsigned long long dbl_order(double d) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(d);
-    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-}
-__device__ __forceinline__ double dbl_unorder(unsigned long long k) {
-    return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
 }
 
 // MODE (SCAN_NN / SCAN_RANGE) is a template parameter so that each
@@ -469,16 +442,20 @@ static hipError_t launch_scan(const ScanArgs &a0, int mode, hipStream_t s) {
 }
 
 hipError_t launch_nn_dist(const DevIndex &ix, const uint8_t *qpad, int64_t nq, double *nn,
-                          unsigned long long *bits, hipStream_t s) {
+                          unsigned long long *bits, uint8_t *ws, hipStream_t s) {
     if (nq == 0) return hipSuccess;
-    hipError_t e = launch_fill_u64(bits, nq, ~0ull, s);
-    if (e != hipSuccess) return e;
     ScanArgs a{};
     a.ix = ix;
     a.qpad = qpad;
     a.nq = nq;
     a.nn_bits = bits;
-    e = launch_scan(a, SCAN_NN, s);
+    hipError_t e = hipSuccess;
+    if (scan_split_ok(ix)) {
+        e = launch_split_nn(a, ws, s);
+    } else {
+        e = launch_fill_u64(bits, nq, ~0ull, s);
+        if (e == hipSuccess) e = launch_scan(a, SCAN_NN, s);
+    }
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_nn_finish, dim3((unsigned)std::min<int64_t>((nq + 255) / 256, 4096)),
                        dim3(256), 0, s, bits, nq, ix.dtype, ix.key_off, nn);
@@ -486,7 +463,7 @@ hipError_t launch_nn_dist(const DevIndex &ix, const uint8_t *qpad, int64_t nq, d
 }
 
 hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth,
-                              int64_t nq, SearchBufs &sb, int num_cus, hipStream_t s) {
+                              int64_t nq, SearchBufs &sb, uint8_t *ws, int num_cus, hipStream_t s) {
     (void)num_cus;
     if (nq == 0) return hipSuccess;
     hipLaunchKernelGGL(k_identity_tasks, dim3((unsigned)std::min<int64_t>((nq + 255) / 256, 4096)),
@@ -506,7 +483,7 @@ hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QTh
     a.item_cursor = &sb.level_cnt[0];
     a.task_cnt = sb.task_cnt;
     a.overflow = &sb.counters[CTR_OVERFLOW];
-    return launch_scan(a, SCAN_RANGE, s);
+    return scan_split_ok(ix) ? launch_split_range(a, ws, s) : launch_scan(a, SCAN_RANGE, s);
 }
 
 } // namespace rr

@@ -1,0 +1,464 @@
+// rr_scan_f32.hip -- dense float32 scan: a bfloat16 filter on the matrix
+// cores in front of the exact FP64 decision.
+//
+// Every value is split into two bfloat16 parts, x = xh + xl + e with
+// |e| <= 2^-18 |x|, and the products qh.xh + qh.xl + ql.xh accumulate in
+// float32 (v_mfma_f32_32x32x16_bf16, three products a step).  A bound on the
+// distance of that sum from q.x (slack, below) turns it into a test that no
+// pair inside the radius can fail; the few pairs that pass are decided, and
+// their distances computed, in FP64 from the float32 rows, chunk by chunk in
+// the order of the graph search's kernels, so a scan and a search report the
+// same bits.
+//
+// What bounds it: the float64 products would take 5.4 ms for 2,000 queries x
+// 1M x 96 values at the 70 TFLOP/s that a large FP64 matrix product reaches
+// on MI355X; three bfloat16 products are 0.9 ms at 1.27 PFLOP/s.  This kernel
+// takes 1.42 ms (0.81 PFLOP/s of products).  The FP64 scan of rr_scan.hip took
+// 30.4 ms (both operands read from memory at every step); it remains for data
+// whose squares leave the float32 range.  Nearest distances (two passes): 2,000
+// queries x 100K x 96 3.24 -> 0.27 ms, one query 74 -> 47 us, 100 queries x
+// 100K x 200 468 -> 281 us.  Relative error of the FP64 results against a
+// 64-bit reference: at most 1.1e-16 (differences), 1.2e-14 before (products).
+//
+// Layout: a workgroup of four waves holds 128 queries, 32 per wave, in
+// registers (both parts; for rows of more than 128 values a step's part) and
+// streams tiles of 64 base points: the tile's float32 rows are loaded one
+// step ahead, split in registers and stored to LDS once for the four waves.
+// Chunks of 16 bytes are stored at (chunk xor a function of the row), so the
+// 16 lanes that read one chunk column of 16 rows fall on different banks.
+// The test of a tile is one maximum over the 16 accumulators of a lane: they
+// start at the query's threshold term, and the point's |x|^2 / 2 is constant
+// along a lane.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+#include "rr_scan.h"
+#include "rr_search.h"
+
+namespace rr {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// SPLIT_MAX: the largest approximate q.x - |x|^2 / 2 of every query;
+// SPLIT_RANGE: hits to the item arrays; SPLIT_MIN: the smallest distance of
+// the pairs that pass
+enum { SPLIT_MAX = 0, SPLIT_RANGE = 1, SPLIT_MIN = 2 };
+
+constexpr int SPLIT_TILE = 64;   // base points per step
+constexpr int SPLIT_Q = 128;     // queries per workgroup
+constexpr int SPLIT_STAGE = 128; // staged candidates per wave
+
+struct SplitArgs {
+    ScanArgs sc;
+    const uint16_t *qs;  // [nq][2][kpad] high and low parts of the queries
+    const float *cinit;  // [nq] what the sums start from
+    unsigned *best;      // [nq] SPLIT_MAX: ordered bits of the largest sum
+    int64_t pblocks;     // a multiple of 8
+    int32_t qblocks, kpad, cpl, g;
+};
+
+__device__ __forceinline__ unsigned flt_order(float f) {
+    const unsigned b = __float_as_uint(f);
+    return (b >> 31) ? ~b : (b | 0x80000000u);
+}
+__device__ __forceinline__ float flt_unorder(unsigned k) {
+    return __uint_as_float((k >> 31) ? (k & 0x7fffffffu) : ~k);
+}
+
+// eight values as bfloat16: the rounded values and what they leave
+__device__ __forceinline__ void split8(f32x8 x, uint4 &hi, uint4 &lo) {
+    hi = __builtin_bit_cast(uint4, __builtin_convertvector(x, bf16x8));
+    const uint32_t w[4] = {hi.x, hi.y, hi.z, hi.w};
+    f32x8 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        r[2 * j] = x[2 * j] - __uint_as_float(w[j] << 16);
+        r[2 * j + 1] = x[2 * j + 1] - __uint_as_float(w[j] & 0xffff0000u);
+    }
+    lo = __builtin_bit_cast(uint4, __builtin_convertvector(r, bf16x8));
+}
+
+// Split queries and their threshold terms, one wave per query.  With s the
+// approximate sum of q.x and M the largest |x|, |s - q.x| is at most
+// 3.1 2^-18 |q| M (the parts left out) plus (3 K + 16) 2^-22 times the
+// magnitudes that the accumulation meets (K values a row; every addition and
+// the comparison within 2^-22 of its operands), plus what underflows.
+// Squared distance: d <= r  <=>  q.x - |x|^2 / 2 >= (|q|^2 - r) / 2; inner
+// product: d <= r  <=>  q.x >= -r.  cinit is the negated right side plus the
+// slack, rounded up.  A query that is not finite or too large to square in
+// float32 gets zero parts and an infinite slack: every pair passes to the
+// FP64 decision.
+__global__ void k_split_prep(const uint8_t *qpad, const QThresh *qth, int64_t nq, int32_t row_bytes,
+                             int32_t d, int32_t kpad, double maxnorm, int ip, uint16_t *qs, float *cinit,
+                             float *slack_out, unsigned *best) {
+    const int lane = threadIdx.x & 63;
+    const int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (q >= nq) return;
+    const float *qr = reinterpret_cast<const float *>(qpad + q * row_bytes);
+    double n2 = 0.0;
+    for (int i = lane; i < d; i += 64) n2 = fma((double)qr[i], (double)qr[i], n2);
+    for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+    const bool ok = n2 <= 1e34;
+    const double qn = sqrt(n2), m = maxnorm * (1.0 + 1e-6);
+    const double acc = (double)(3 * kpad + 16) * 0x1p-22;
+    const double r = qth ? qth[q].r : 0.0;
+    double slack = (3.2 * 0x1p-18 + acc) * qn * m + acc * 0.5 * (n2 + m * m + (qth ? fabs(r) : qn * m)) +
+                   (qn + m) * (double)kpad * 0x1p-120 + 1e-30;
+    if (!ok) slack = __builtin_huge_val();
+    uint4 *hi = reinterpret_cast<uint4 *>(qs + (size_t)q * 2 * kpad), *lo = hi + kpad / 8;
+    const int cols = row_bytes / 4;
+    for (int c = lane; c < kpad / 8; c += 64) {
+        f32x8 x = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (ok && c * 8 < cols) x = *reinterpret_cast<const f32x8 *>(qr + c * 8);
+        uint4 h, l;
+        split8(x, h, l);
+        hi[c] = h;
+        lo[c] = l;
+    }
+    if (lane == 0) {
+        cinit[q] = ok ? __double2float_ru((ip ? r : 0.5 * (r - n2)) + slack) : __builtin_huge_valf();
+        slack_out[q] = __double2float_ru(slack);
+        best[q] = 0u; // below the ordered bits of every sum
+    }
+}
+
+// SPLIT_MIN's start: a pair can hold the query's smallest distance only if
+// its sum comes within two slacks of the largest sum
+__global__ void k_split_best(const unsigned *best, const float *slack, int64_t nq, float *cinit,
+                             unsigned long long *nn_bits) {
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= nq) return;
+    // (an infinite slack passes every pair, whatever the sums were)
+    const double s = (double)slack[q];
+    cinit[q] = s <= 1e38 ? __double2float_ru(2.0 * s - (double)flt_unorder(best[q])) : __builtin_huge_valf();
+    nn_bits[q] = dbl_order(__builtin_huge_val());
+}
+
+// The staged pairs of one wave, decided in FP64: groups of g lanes read a
+// pair's rows, each lane cpl chunks, summed as eval_rows sums them.  Hits are
+// compacted in place (a round's reads precede its writes, which land at or
+// below its first entry) and appended to the item arrays with one cursor
+// atomic (SPLIT_RANGE), or lower their query's minimum (SPLIT_MIN).
+template <int MODE>
+__device__ __forceinline__ void split_flush(const SplitArgs &a, uint32_t *st_q, uint32_t *st_id,
+                                            double *st_d, int n, int lane) {
+    wave_sync();
+    const int g = a.g, cpl = a.cpl, gl = lane & (g - 1), per = 64 / g;
+    const bool ip = a.sc.ix.metric == RR_IP;
+    const size_t rb = a.sc.ix.row_bytes;
+    int kept = 0;
+    for (int e0 = 0; e0 < n; e0 += per) {
+        const int e = e0 + lane / g;
+        const uint32_t q = st_q[min(e, n - 1)], id = st_id[min(e, n - 1)];
+        const uint4 *x = reinterpret_cast<const uint4 *>(a.sc.ix.base + id * rb) + gl * cpl;
+        const uint4 *y = reinterpret_cast<const uint4 *>(a.sc.qpad + q * rb) + gl * cpl;
+        double s = 0.0;
+        for (int k = 0; k < cpl; ++k) s += ip ? chunk_ip<RR_F32>(x[k], y[k]) : chunk_part<RR_F32>(x[k], y[k]);
+        for (int o = 1; o < g; o <<= 1) s += __shfl_xor(s, o);
+        if (ip) s = -s;
+        const bool mine = gl == 0 && e < n;
+        if (MODE == SPLIT_MIN) {
+            if (mine && s <= __builtin_huge_val()) atomicMin(&a.sc.nn_bits[q], dbl_order(s));
+        } else {
+            const bool hit = mine && s <= a.sc.qth[q].r;
+            const unsigned long long hm = __ballot(hit);
+            wave_sync();
+            if (hit) {
+                const int o = kept + mbcnt(hm);
+                st_q[o] = q;
+                st_id[o] = id;
+                st_d[o] = s;
+            }
+            kept += __popcll(hm);
+        }
+        wave_sync();
+    }
+    if (MODE == SPLIT_RANGE && kept > 0) {
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(a.sc.item_cursor, (unsigned long long)kept);
+        base = __shfl(base, 0);
+        for (int i = lane; i < kept; i += 64) {
+            const int64_t pos = (int64_t)base + i;
+            if (pos < a.sc.item_cap) {
+                a.sc.item_key[pos] = ((unsigned long long)st_q[i] << 32) | st_id[i];
+                ((double *)a.sc.item_dist)[pos] = st_d[i];
+                atomicAdd(&a.sc.task_cnt[st_q[i]], 1ull);
+            }
+        }
+        if (lane == 0 && (int64_t)base + kept > a.sc.item_cap) atomicOr(a.sc.overflow, 64ull);
+        wave_sync();
+    }
+}
+
+// KS: 16-value steps held at a time (even); MULTI: rows of more than 16 KS
+// values take several passes over a tile, the sums kept in between
+template <int KS, bool MULTI, int MODE>
+__global__ __launch_bounds__(256, 2) void k_scan_split(SplitArgs a) {
+    constexpr int CPR = 2 * KS;       // 16-byte chunks per row and part
+    constexpr int UNITS = KS / 2;     // chunks a thread splits per step
+    constexpr int PART = SPLIT_TILE * CPR;
+    extern __shared__ __align__(16) uint8_t smem[];
+    uint4 *xt = reinterpret_cast<uint4 *>(smem); // [2 buffers][2 parts][PART]
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    double *st_d = reinterpret_cast<double *>(smem + 4 * PART * 16) + wid * SPLIT_STAGE;
+    uint32_t *st_q = reinterpret_cast<uint32_t *>(smem + 4 * PART * 16 + 4 * SPLIT_STAGE * 8) + wid * 2 * SPLIT_STAGE;
+    uint32_t *st_id = st_q + SPLIT_STAGE;
+    // the query blocks of one chunk of the base follow each other on one XCD
+    // (workgroups are dealt to the 8 XCDs in turn), so its L2 serves them
+    const int64_t lin = blockIdx.x;
+    const int64_t pb = lin % 8 + 8 * ((lin / 8) / a.qblocks);
+    const int64_t q0 = ((lin / 8) % a.qblocks) * SPLIT_Q + wid * 32;
+    const int64_t p_begin = pb * a.sc.chunk, p_end = min(a.sc.ix.n, p_begin + a.sc.chunk);
+    if (p_begin >= p_end) return;
+    const bool active = q0 < a.sc.nq; // waves without queries only help to load
+    const bool ip = a.sc.ix.metric == RR_IP;
+    const int cols = a.sc.ix.row_bytes / 4;
+    const int nkc = MULTI ? a.kpad / (KS * 16) : 1;
+    const int half = lane >> 5, l32 = lane & 31;
+    auto swz = [](int row) { return KS == 8 ? row & 15 : KS == 4 ? (row >> 1) & 7 : (row >> 2) & 3; };
+
+    f32x8 nx[UNITS];
+    auto load_x = [&](int64_t p0, int kc) {
+#pragma unroll
+        for (int j = 0; j < UNITS; ++j) {
+            const int u = tid + 256 * j, row = u / CPR, c = u % CPR;
+            const int64_t p = min(p0 + row, p_end - 1);
+            const int col = kc * KS * 16 + c * 8;
+            if (col < cols) {
+                nx[j] = *reinterpret_cast<const f32x8 *>(a.sc.ix.base + p * a.sc.ix.row_bytes + col * 4);
+            } else {
+                nx[j] = f32x8{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    };
+    auto store_x = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < UNITS; ++j) {
+            const int u = tid + 256 * j, row = u / CPR, c = u % CPR;
+            uint4 h, l;
+            split8(nx[j], h, l);
+            const int o = row * CPR + (c ^ swz(row));
+            xt[2 * buf * PART + o] = h;
+            xt[(2 * buf + 1) * PART + o] = l;
+        }
+    };
+    // A operand: lane l holds query l % 32, values 16 k + 8 (l / 32) + [0, 8)
+    bf16x8 Ah[KS], Al[KS];
+    auto load_q = [&](int kc) {
+        const int64_t q = min(q0 + l32, a.sc.nq - 1);
+        const uint16_t *r = a.qs + (size_t)q * 2 * a.kpad + kc * KS * 16 + half * 8;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            Ah[k] = *reinterpret_cast<const bf16x8 *>(r + 16 * k);
+            Al[k] = *reinterpret_cast<const bf16x8 *>(r + a.kpad + 16 * k);
+        }
+    };
+    if (active && !MULTI) load_q(0);
+    // output tile: lane l, register v holds query 8 (v / 4) + 4 (l / 32) + v % 4
+    // and point l % 32
+    f32x16 c0, lim;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int64_t q = q0 + 8 * (v / 4) + 4 * half + v % 4;
+        c0[v] = MODE == SPLIT_MAX ? 0.f : q < a.sc.nq ? a.cinit[q] : -__builtin_huge_valf();
+        lim[v] = -__builtin_huge_valf();
+    }
+    int scnt = 0; // staged candidates of this wave (wave-uniform)
+    f32x16 acc[2];
+    load_x(p_begin, 0);
+    int buf = 0;
+    for (int64_t p0 = p_begin; p0 < p_end; p0 += SPLIT_TILE) {
+        float hx[2];
+        bool pv[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int64_t p = p0 + 32 * t + l32;
+            pv[t] = p < p_end;
+            hx[t] = ip ? 0.f : a.sc.ix.half_norm[min(p, p_end - 1)];
+            acc[t] = c0;
+        }
+        for (int kc = 0; kc < nkc; ++kc) {
+            if (MULTI && active) load_q(kc);
+            store_x(buf);
+            __syncthreads();
+            if (kc + 1 < nkc) load_x(p0, kc + 1);
+            else if (p0 + SPLIT_TILE < p_end) load_x(p0 + SPLIT_TILE, 0);
+            if (active) {
+#pragma unroll
+                for (int k = 0; k < KS; ++k) {
+                    bf16x8 bh[2], bl[2];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const int row = 32 * t + l32;
+                        const int o = row * CPR + ((2 * k + half) ^ swz(row));
+                        bh[t] = __builtin_bit_cast(bf16x8, xt[2 * buf * PART + o]);
+                        bl[t] = __builtin_bit_cast(bf16x8, xt[(2 * buf + 1) * PART + o]);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Ah[k], bh[t], acc[t], 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Ah[k], bl[t], acc[t], 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Al[k], bh[t], acc[t], 0, 0, 0);
+                }
+            }
+            // the other buffer is free: every wave has passed this step's
+            // barrier, so it is done with the step before
+            buf ^= 1;
+        }
+        if (!active) continue;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (MODE == SPLIT_MAX) {
+                if (pv[t]) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) lim[v] = fmaxf(lim[v], acc[t][v] - hx[t]);
+                }
+                continue;
+            }
+            float top = acc[t][0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) top = fmaxf(top, acc[t][v]);
+            if (!__ballot(pv[t] && top >= hx[t])) continue;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const bool cand = pv[t] && acc[t][v] >= hx[t];
+                const unsigned long long cm = __ballot(cand);
+                if (!cm) continue;
+                const int nc = __popcll(cm);
+                if (scnt + nc > SPLIT_STAGE) {
+                    split_flush<MODE>(a, st_q, st_id, st_d, scnt, lane);
+                    scnt = 0;
+                }
+                if (cand) {
+                    const int o = scnt + mbcnt(cm);
+                    st_q[o] = (uint32_t)(q0 + 8 * (v / 4) + 4 * half + v % 4);
+                    st_id[o] = (uint32_t)(p0 + 32 * t + l32);
+                }
+                scnt += nc;
+            }
+        }
+    }
+    if (!active) return;
+    if (MODE == SPLIT_MAX) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            float m = lim[v];
+            for (int o = 1; o < 32; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+            const int64_t q = q0 + 8 * (v / 4) + 4 * half + v % 4;
+            if (l32 == 0 && q < a.sc.nq) atomicMax(&a.best[q], flt_order(m));
+        }
+    } else if (scnt > 0) {
+        split_flush<MODE>(a, st_q, st_id, st_d, scnt, lane);
+    }
+}
+
+// float32 squares of the base and of the products must be normal numbers:
+// otherwise the FP64 scan runs
+bool scan_split_ok(const DevIndex &ix) {
+    return ix.dtype == RR_F32 && ix.half_norm && ix.max_norm >= 1e-12f && ix.max_norm <= 1e17f;
+}
+
+static int split_ks(int32_t d) { return d <= 32 ? 2 : d <= 64 ? 4 : d <= 96 ? 6 : 8; }
+static int32_t split_kpad(int32_t d) {
+    const int32_t k = split_ks(d) * 16;
+    return (d + k - 1) / k * k;
+}
+
+// split queries, then the threshold term, the slack and the best sum of
+// every query; per query a multiple of 16 bytes
+int64_t scan_ws_row(const DevIndex &ix) {
+    return scan_split_ok(ix) ? (int64_t)split_kpad(ix.d) * 4 + 16 : 0;
+}
+
+struct SplitWs {
+    uint16_t *qs;
+    float *cinit, *slack;
+    unsigned *best;
+};
+static SplitWs split_ws(const DevIndex &ix, int64_t nq, uint8_t *ws) {
+    SplitWs w;
+    w.qs = reinterpret_cast<uint16_t *>(ws);
+    w.cinit = reinterpret_cast<float *>(ws + nq * (int64_t)split_kpad(ix.d) * 4);
+    w.slack = w.cinit + nq;
+    w.best = reinterpret_cast<unsigned *>(w.slack + nq);
+    return w;
+}
+
+template <int KS, bool MULTI, int MODE> static hipError_t run_split(SplitArgs &a, hipStream_t s) {
+    const size_t shmem = (size_t)4 * SPLIT_TILE * 2 * KS * 16 + 4 * SPLIT_STAGE * 16;
+    int per_cu = 0;
+    auto kern = k_scan_split<KS, MULTI, MODE>;
+    const hipError_t e = kernel_occupancy((const void *)kern, 256, shmem, &per_cu);
+    if (e != hipSuccess) return e;
+    if (per_cu < 1) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.qblocks * a.pblocks)), dim3(256), shmem, s, a);
+    return hipGetLastError();
+}
+
+template <int MODE> static hipError_t dispatch_split(SplitArgs &a, hipStream_t s) {
+    switch (split_ks(a.sc.ix.d)) {
+    case 2: return run_split<2, false, MODE>(a, s);
+    case 4: return run_split<4, false, MODE>(a, s);
+    case 6: return run_split<6, false, MODE>(a, s);
+    default: return a.kpad <= 128 ? run_split<8, false, MODE>(a, s) : run_split<8, true, MODE>(a, s);
+    }
+}
+
+static hipError_t split_setup(const ScanArgs &sc, uint8_t *ws, SplitArgs &a, SplitWs &w, hipStream_t s) {
+    w = split_ws(sc.ix, sc.nq, ws);
+    a.sc = sc;
+    a.qs = w.qs;
+    a.cinit = w.cinit;
+    a.best = w.best;
+    a.kpad = split_kpad(sc.ix.d);
+    row_split(sc.ix.row_bytes, &a.cpl, &a.g);
+    a.qblocks = (int32_t)((sc.nq + SPLIT_Q - 1) / SPLIT_Q);
+    // about 4,096 workgroups (512 are resident), a chunk of whole tiles each
+    int64_t pb = std::max<int64_t>(8, 4096 / a.qblocks);
+    const int64_t tiles = (sc.ix.n + SPLIT_TILE - 1) / SPLIT_TILE;
+    a.sc.chunk = (tiles + pb - 1) / pb * SPLIT_TILE;
+    pb = (sc.ix.n + a.sc.chunk - 1) / a.sc.chunk;
+    a.pblocks = (pb + 7) / 8 * 8;
+    hipLaunchKernelGGL(k_split_prep, dim3((unsigned)((sc.nq + 3) / 4)), dim3(256), 0, s, sc.qpad, sc.qth, sc.nq,
+                       sc.ix.row_bytes, sc.ix.d, a.kpad, (double)sc.ix.max_norm, (int)(sc.ix.metric == RR_IP),
+                       w.qs, w.cinit, w.slack, w.best);
+    return hipGetLastError();
+}
+
+hipError_t launch_split_range(const ScanArgs &sc, uint8_t *ws, hipStream_t s) {
+    SplitArgs a;
+    SplitWs w;
+    const hipError_t e = split_setup(sc, ws, a, w, s);
+    return e != hipSuccess ? e : dispatch_split<SPLIT_RANGE>(a, s);
+}
+
+// Two passes: the largest approximate sum of every query, then the pairs
+// within two slacks of it, decided in FP64.  One pass with a running bound
+// would hand over every record of every lane's sequence (about 80 per query
+// and chunk) instead of a few pairs per query.
+hipError_t launch_split_nn(const ScanArgs &sc, uint8_t *ws, hipStream_t s) {
+    SplitArgs a;
+    SplitWs w;
+    ScanArgs sc0 = sc;
+    sc0.qth = nullptr;
+    hipError_t e = split_setup(sc0, ws, a, w, s);
+    if (e != hipSuccess) return e;
+    e = dispatch_split<SPLIT_MAX>(a, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_split_best, dim3((unsigned)((sc.nq + 255) / 256)), dim3(256), 0, s, w.best, w.slack,
+                       sc.nq, w.cinit, sc.nn_bits);
+    e = hipGetLastError();
+    return e != hipSuccess ? e : dispatch_split<SPLIT_MIN>(a, s);
+}
+
+} // namespace rr
