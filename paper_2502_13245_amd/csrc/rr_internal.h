@@ -69,7 +69,7 @@ struct QThresh {
 // Resumable state of one query's beam phase (the serving loop runs the beam
 // kernel in ticks with a step budget; B itself is stored beside it).
 struct BeamState {
-    int32_t nB, visits, evals, cursor;
+    int32_t nB, visits, evals;
     int32_t flags; // BS_* below
     int32_t edges; // adjacency entries read so far
 };

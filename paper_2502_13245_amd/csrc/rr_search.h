@@ -69,21 +69,37 @@ template <> __device__ __forceinline__ float dmax<float>() { return __builtin_hu
 
 __device__ __forceinline__ uint32_t hash32(uint32_t x) { return x * 2654435761u; }
 
-// LDS seen-cache: open addressing, `probes` linear probes.  Returns true if
-// `id` was already present.  When every probe slot is taken by other ids the
-// id is not recorded (the cache forgets it) and `overflow` is set.
-__device__ __forceinline__ bool seen_insert(uint32_t *tab, uint32_t cs_mask, uint32_t id,
-                                            bool &overflow) {
-    uint32_t h = hash32(id);
-#pragma unroll 1
-    for (int p = 0; p < 8; ++p) {
-        uint32_t slot = (h + (uint32_t)p) & cs_mask;
-        uint32_t old = atomicCAS(&tab[slot], RR_EMPTY32, id);
-        if (old == RR_EMPTY32) return false;
-        if (old == id) return true;
+// LDS seen-cache of cs ids (a power of two, at least 64) in buckets of
+// eight; `shift` is 32 - log2(cs / 8).  Returns true if `id` was already
+// present.  A full bucket loses one of its ids to the new one (the cache
+// forgets it) and `overflow` is set.  One pair of 16-byte reads decides a
+// bucket where a linear probe would take up to eight dependent atomics, and
+// a long search keeps its recent ids, which are the ones that come back.
+__device__ __forceinline__ bool seen_insert(uint32_t *tab, int shift, uint32_t id, bool &overflow) {
+    const uint32_t h = id * 2654435761u;
+    uint32_t *const bk = tab + 8 * (h >> shift);
+    for (;;) {
+        const uint4 u = reinterpret_cast<const uint4 *>(bk)[0], v = reinterpret_cast<const uint4 *>(bk)[1];
+        const uint32_t w[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+        uint32_t diff = ~0u, empty = 0u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            diff = min(diff, w[j] ^ id);
+            empty |= w[j] == RR_EMPTY32 ? 1u << j : 0u;
+        }
+        if (diff == 0u) return true;
+        // the first empty slot from a place of the id's own, so that lanes
+        // that meet in a bucket seldom want the same slot
+        const uint32_t at = (h >> 4) & 7u;
+        if (empty == 0u) {
+            bk[at] = id;
+            overflow = true;
+            return false;
+        }
+        const uint32_t e = ((uint32_t)__ffs((int)((empty | empty << 8) >> at)) - 1u + at) & 7u;
+        // another lane may take the slot first (the ids of one visit differ)
+        if (atomicCAS(bk + e, RR_EMPTY32, id) == RR_EMPTY32) return false;
     }
-    overflow = true;
-    return false;
 }
 
 // Global exact set of (task, id) keys: returns true if the key was inserted
@@ -202,20 +218,26 @@ __device__ __forceinline__ int64_t xcd_block() {
     return (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
 }
 
-// the value of lane (lane ^ J) for a compile-time J, without the address
-// arithmetic and LDS round trip of ds_bpermute: DPP quad permutes for 1 and
-// 2, ds_swizzle in bit mode (xor mask, within 32 lanes) for 4, 8 and 16, and
-// for 32 the permlane32 swap (lanes 32-63 of one copy trade places with lanes
-// 0-31 of another: the first copy's upper half then holds the lower half's
-// values, the second copy's lower half the upper half's).  Every lane of the
-// wave must be active.
+// the value of lane (lane ^ J) for a compile-time J, in the VALU alone (no
+// LDS round trip): DPP quad permutes for 1 and 2, a half-row mirror (lane ^ 7)
+// and a quad reversal (lane ^ 3) for 4, a row rotation for 8, and the
+// permlane swaps for 16 and 32 (odd rows of one copy trade places with even
+// rows of another, or lanes 32-63 with lanes 0-31: the first copy's upper
+// part then holds the lower part's values, the second copy's lower part the
+// upper part's).  Every lane of the wave must be active.
 template <int J> __device__ __forceinline__ uint32_t xor_lane(uint32_t v) {
     if constexpr (J == 1) {
         return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);
     } else if constexpr (J == 2) {
         return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);
-    } else if constexpr (J < 32) {
-        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x1F | (J << 10));
+    } else if constexpr (J == 4) {
+        const int m = __builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);
+        return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1B, 0xF, 0xF, false);
+    } else if constexpr (J == 8) {
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, false);
+    } else if constexpr (J == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (lane_id() & 16) ? r[0] : r[1];
     } else {
         const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
         return (lane_id() & 32) ? r[0] : r[1];
@@ -240,6 +262,27 @@ template <int G, typename T> __device__ __forceinline__ T group_sum(T v) {
     if constexpr (G >= 32) v += xor_lane_d<16>(v);
     if constexpr (G >= 64) v += xor_lane_d<32>(v);
     return v;
+}
+
+// v[0, N): partial sums of N rounds held by every lane of a group of G.
+// Exchanges at distances J, 2J, ... up to G/2: while a lane holds several
+// rounds it keeps one half (the lower for a clear lane bit) and adds what the
+// other lane held of it; v[0] ends as the group's sum of one round.
+template <int J, int N, int G, typename T> __device__ __forceinline__ void scatter_sum(T *v, int lane) {
+    if constexpr (J < G) {
+        if constexpr (N > 1) {
+            const bool up = (lane & J) != 0;
+#pragma unroll
+            for (int i = 0; i < N / 2; ++i) {
+                const T keep = up ? v[i + N / 2] : v[i], send = up ? v[i] : v[i + N / 2];
+                v[i] = keep + xor_lane_d<J>(send);
+            }
+            scatter_sum<2 * J, N / 2, G>(v, lane);
+        } else {
+            v[0] += xor_lane_d<J>(v[0]);
+            scatter_sum<2 * J, 1, G>(v, lane);
+        }
+    }
 }
 
 // one compare-exchange stage of the bitonic network (merge size K, distance J)
@@ -291,22 +334,6 @@ template <typename D> __device__ __forceinline__ void wave_sort(D &d, uint32_t &
     bitonic_stage<64, 4>(d, id, lane);
     bitonic_stage<64, 2>(d, id, lane);
     bitonic_stage<64, 1>(d, id, lane);
-}
-
-// number of entries of the sorted arrays (ad, ai)[0, n) that are < (d, id);
-// ids compared without the visited bit
-template <typename D>
-__device__ __forceinline__ int lower_bound_key(const D *ad, const uint32_t *ai, int n, D d,
-                                               uint32_t id) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (key_less(ad[mid], ai[mid] & RR_IDMASK, d, id))
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
 }
 
 // --------------------------------------------------------------------------
@@ -614,6 +641,78 @@ __device__ __forceinline__ void eval_rows(const DevIndex &ix, const QueryRegs<DT
     wave_sync();
 }
 
+// Evaluate up to 64 candidates ci[0, k) (ids in LDS), one per lane: returns
+// the distance of candidate `c` of this lane (meaningless where c >= k).  Row
+// r of a batch of RB rounds is read by lane group r % (64/G); the sums over a
+// group's lanes are reduced and scattered at once: at each exchange distance a
+// lane passes on half of its rounds and keeps the other half, so RB rounds
+// take RB - 1 exchanges instead of RB log2(RB), and every lane ends with one
+// round's sum.  The additions pair the same lanes in the same order as
+// group_sum.  8 to 12 chunk loads of a lane are in flight.
+template <int DTYPE, int CPL, int G>
+__device__ __forceinline__ typename DistOf<DTYPE>::T eval64(const DevIndex &ix, const QueryRegs<DTYPE, CPL, G> &qr,
+                                                            const uint32_t *ci, int k, int &c) {
+    using D = typename DistOf<DTYPE>::T;
+    using Acc = typename DistOf<DTYPE>::Acc;
+    constexpr int RPR = 64 / G; // rows per round
+    constexpr int RBX = CPL == 1 ? 8 : CPL <= 3 ? 4 : 2;
+    constexpr int RB = RBX < G ? RBX : G, NB = G / RB; // rounds per batch, batches
+    const int lane = lane_id();
+    const int gl = lane & (G - 1);
+    const int grp = lane / G;
+    Acc out = 0;
+    const int mysel = (lane / RB) & (NB - 1);
+#pragma unroll
+    for (int bt = 0; bt < NB; ++bt) {
+        if (bt * RB * RPR >= k) break;
+        // every lane loads (past the end, the last candidate's row again): all
+        // ids are read before the first load, and no load waits on a branch
+        const uint8_t *row[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const uint32_t id = ci[min((bt * RB + r) * RPR + grp, k - 1)];
+            row[r] = ix.base + (uint64_t)id * (uint32_t)ix.row_bytes + gl * CPL * 16;
+        }
+        uint4 buf[RB][CPL];
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int kk = 0; kk < CPL; ++kk) buf[r][kk] = *reinterpret_cast<const uint4 *>(row[r] + kk * 16);
+        Acc v[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            Acc a = 0;
+#pragma unroll
+            for (int kk = 0; kk < CPL; ++kk) {
+                if constexpr (DTYPE == RR_BF16X)
+                    a += chunk_part_bf16(buf[r][kk], qr.c[2 * kk], qr.c[2 * kk + 1]);
+                else if constexpr (DTYPE == RR_BF16XIP)
+                    a += chunk_ip_bf16(buf[r][kk], qr.c[2 * kk], qr.c[2 * kk + 1]);
+                else if constexpr (DTYPE == RR_SQ8X)
+                    a += chunk_part_sq8(buf[r][kk], &qr.c[4 * kk]);
+                else if constexpr (DTYPE == RR_SQ8XIP)
+                    a += chunk_ip_sq8(buf[r][kk], &qr.c[4 * kk]);
+                else if constexpr (dip(DTYPE))
+                    a += chunk_ip<dbase(DTYPE)>(buf[r][kk], qr.c[kk]);
+                else
+                    a += chunk_part<DTYPE>(buf[r][kk], qr.c[kk]);
+            }
+            v[r] = a;
+        }
+        scatter_sum<1, RB, G>(v, lane);
+        out = mysel == bt ? v[0] : out;
+    }
+    // the round a lane ended with: bit s of the lane chose the half of RB >> s
+    int r = 0;
+#pragma unroll
+    for (int s = 0; (RB >> s) > 1; ++s) r += ((lane >> s) & 1) * (RB >> (s + 1));
+    c = (mysel * RB + r) * RPR + grp;
+    if constexpr (dbase(DTYPE) == RR_SQ8X) return (D)(out * qr.sc);
+    else if constexpr (dfloat(DTYPE)) return (D)(dip(DTYPE) ? -out : out);
+    else if constexpr (dip(DTYPE)) return (D)((uint32_t)qr.qq - (uint32_t)out);
+    else return (D)(uint32_t)(out + qr.qq);
+}
+
 // in-range test and early-stop tests on the exact distance
 template <typename D> __device__ __forceinline__ bool in_range(D d, const QThresh &t);
 template <> __device__ __forceinline__ bool in_range<uint32_t>(uint32_t d, const QThresh &t) {
@@ -657,6 +756,449 @@ template <int DTYPE> __device__ __forceinline__ size_t qrow_stride(const DevInde
 }
 
 // --------------------------------------------------------------------------
+// the beam of one wave
+// --------------------------------------------------------------------------
+
+// Beam keys: the (d, id) order as unsigned integers.  The distance is mapped
+// to an unsigned image in its order (-0 as +0, NaN last), the id is shifted
+// left by one, and bit 0 says whether the point was visited (two keys of one
+// beam never differ in that bit alone).  All ones is the empty key: it is
+// after every other and counts as visited.
+__device__ __forceinline__ uint32_t key_image(uint32_t d) { return d; }
+__device__ __forceinline__ uint32_t key_image(float d) {
+    const uint32_t b = __float_as_uint(d + 0.f);
+    return d == d ? ((b >> 31) ? ~b : (b | 0x80000000u)) : 0xffffffffu;
+}
+__device__ __forceinline__ uint64_t key_image(double d) {
+    const uint64_t b = (uint64_t)__double_as_longlong(d + 0.0);
+    return d == d ? ((b >> 63) ? ~b : (b | 0x8000000000000000ull)) : ~0ull;
+}
+template <typename D> __device__ __forceinline__ D key_unimage(uint64_t k);
+template <> __device__ __forceinline__ uint32_t key_unimage<uint32_t>(uint64_t k) { return (uint32_t)k; }
+template <> __device__ __forceinline__ float key_unimage<float>(uint64_t k) {
+    const uint32_t u = (uint32_t)k;
+    return __uint_as_float((u >> 31) ? (u & 0x7fffffffu) : ~u);
+}
+template <> __device__ __forceinline__ double key_unimage<double>(uint64_t k) {
+    return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
+}
+
+__device__ __forceinline__ uint32_t read_lane(uint32_t v, int j) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, j);
+}
+// lane 0's value, known to be uniform
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// 32-bit distances: one 64-bit word.  FP64 distances: a 64-bit and a 32-bit word.
+template <typename D> struct BeamKey {
+    uint64_t v;
+    static __device__ __forceinline__ BeamKey make(D d, uint32_t id) {
+        return {((uint64_t)key_image(d) << 32) | (uint64_t)(id << 1)};
+    }
+    static __device__ __forceinline__ BeamKey empty() { return {~0ull}; }
+    __device__ __forceinline__ bool less(const BeamKey &o) const { return v < o.v; }
+    __device__ __forceinline__ bool same(const BeamKey &o) const { return (v | 1ull) == (o.v | 1ull); }
+    __device__ __forceinline__ bool visited() const { return (v & 1ull) != 0; }
+    __device__ __forceinline__ void visit() { v |= 1ull; }
+    __device__ __forceinline__ bool is_empty() const { return v == ~0ull; }
+    __device__ __forceinline__ uint32_t id() const { return (uint32_t)v >> 1; }
+    __device__ __forceinline__ D dist() const { return key_unimage<D>(v >> 32); }
+    __device__ __forceinline__ BeamKey lane(int j) const {
+        return {((uint64_t)read_lane((uint32_t)(v >> 32), j) << 32) | read_lane((uint32_t)v, j)};
+    }
+    template <int J> __device__ __forceinline__ BeamKey xored() const {
+        return {((uint64_t)xor_lane<J>((uint32_t)(v >> 32)) << 32) | xor_lane<J>((uint32_t)v)};
+    }
+};
+template <> struct BeamKey<double> {
+    uint64_t d;
+    uint32_t i;
+    static __device__ __forceinline__ BeamKey make(double x, uint32_t id) { return {key_image(x), id << 1}; }
+    static __device__ __forceinline__ BeamKey empty() { return {~0ull, 0xffffffffu}; }
+    __device__ __forceinline__ bool less(const BeamKey &o) const { return d < o.d || (d == o.d && i < o.i); }
+    __device__ __forceinline__ bool same(const BeamKey &o) const { return d == o.d && (i | 1u) == (o.i | 1u); }
+    __device__ __forceinline__ bool visited() const { return (i & 1u) != 0; }
+    __device__ __forceinline__ void visit() { i |= 1u; }
+    __device__ __forceinline__ bool is_empty() const { return d == ~0ull && i == 0xffffffffu; }
+    __device__ __forceinline__ uint32_t id() const { return i >> 1; }
+    __device__ __forceinline__ double dist() const { return key_unimage<double>(d); }
+    __device__ __forceinline__ BeamKey lane(int j) const {
+        return {((uint64_t)read_lane((uint32_t)(d >> 32), j) << 32) | read_lane((uint32_t)d, j), read_lane(i, j)};
+    }
+    template <int J> __device__ __forceinline__ BeamKey xored() const {
+        return {((uint64_t)xor_lane<J>((uint32_t)(d >> 32)) << 32) | xor_lane<J>((uint32_t)d), xor_lane<J>(i)};
+    }
+};
+
+// one compare-exchange stage: a lane keeps the smaller key where `lower` (its
+// bit J clear) equals `up`
+template <int J, typename K> __device__ __forceinline__ void key_stage(K &k, bool up, int lane) {
+    const K o = k.template xored<J>();
+    if (o.less(k) == (((lane & J) == 0) == up)) k = o;
+}
+template <int K0, int J, typename K> __device__ __forceinline__ void key_merge_steps(K &k, bool up, int lane) {
+    key_stage<J>(k, up, lane);
+    if constexpr (J > 1) key_merge_steps<K0, J / 2>(k, up, lane);
+}
+template <int S, typename K> __device__ __forceinline__ void key_sort_steps(K &k, bool up, int lane) {
+    if constexpr (S > 2) key_sort_steps<S / 2>(k, up, lane);
+    key_merge_steps<S, S / 2>(k, ((lane & S) == 0) == up, lane);
+}
+
+// Algorithm 1's beam B: the b best keys seen, visited or not.
+//
+// b <= 64: one key per lane, in order, empty keys above.  The ranks of new
+// keys among the old ones and among themselves are population counts of one
+// comparison each, and one trip through LDS puts every key in its lane; many
+// at once are sorted and merged as two halves of a bitonic sequence.
+//
+// b > 64: a sorted array in LDS (`main`) plus up to 64 later keys in the
+// lanes (`side`), which are merged into the array when they no longer fit
+// the lanes: the array is moved once per about 64 insertions instead of at
+// every visit.  Together they may hold more than b keys; a key whose rank
+// among all of them is b or more is out of B, and stays out, because ranks
+// only grow.  It is never handed out, and the merge drops it.  Once the seen
+// cache has forgotten ids, new keys are looked up in main first (dropping the
+// repeated ones only when they are merged or handed out was slower, 9.3 against
+// 5.1 ms for 1,000 queries at b = 1,024: most of them are repeats by then).
+//
+// Both forms are about latency: a wave's visits form a chain, and the work
+// between its two trips to memory is on it.  Beam kernel times when the beam
+// was a sorted LDS array merged at every visit by binary searches, and now
+// (1M x 128 uint8): 64 queries at b = 32 0.33 -> 0.16 ms; 10,000 at b = 8 0.34
+// -> 0.22 ms; 1,000 at b = 1,024 8.5 -> 4.1 ms; doubling to 4,096 20 -> 5.9 ms.
+template <typename D> struct WaveBeam {
+    using K = BeamKey<D>;
+    static constexpr bool WIDE_KEY = sizeof(D) == 8;
+    uint64_t *mv; // main, in LDS: the keys, or the distances of FP64 keys
+    uint32_t *mi; // FP64 keys: their second words
+    uint64_t *xv; // scratch keys, laid out the same
+    uint32_t *xi;
+    int b;
+    K side;       // this lane's key
+    int ns = 0;   // keys in the lanes
+    int nM = 0;   // wide: keys in main
+    K ck;         // wide: this lane's key of main's chunk at cbase (-1: none)
+    int cbase = -1;
+    int cursor = 0; // wide: main entries before it are visited
+    int im = -1;  // wide: first unvisited entry of main (nM: none; -1: look)
+    K km;         // its key
+    K bound;      // keys not below it cannot enter
+
+    __device__ __forceinline__ bool wide() const { return b > 64; }
+    __device__ __forceinline__ K main_at(int i) const {
+        if constexpr (WIDE_KEY) return K{mv[i], mi[i]};
+        else return K{mv[i]};
+    }
+    __device__ __forceinline__ void main_set(int i, const K &k) {
+        if constexpr (WIDE_KEY) {
+            mv[i] = k.d;
+            mi[i] = k.i;
+        } else {
+            mv[i] = k.v;
+        }
+    }
+    __device__ __forceinline__ K scratch_at(int i) const {
+        if constexpr (WIDE_KEY) return K{xv[i], xi[i]};
+        else return K{xv[i]};
+    }
+    __device__ __forceinline__ void scratch_set(int i, const K &k) {
+        if constexpr (WIDE_KEY) {
+            xv[i] = k.d;
+            xi[i] = k.i;
+        } else {
+            xv[i] = k.v;
+        }
+    }
+    static __device__ __forceinline__ K pick(bool c, const K &a, const K &o) {
+        K r;
+        if constexpr (WIDE_KEY) {
+            r.d = c ? a.d : o.d;
+            r.i = c ? a.i : o.i;
+        } else {
+            r.v = c ? a.v : o.v;
+        }
+        return r;
+    }
+
+    // scratch: 64 keys, and a bit for every key of main
+    static __host__ __device__ __forceinline__ int scratch_keys(int bcap) { return bcap > 4096 ? bcap / 64 : 64; }
+    // lds: scratch_keys(bcap) + bcap keys
+    __device__ __forceinline__ void init(uint8_t *lds, int bcap, int width) {
+        const int sk = scratch_keys(bcap);
+        xv = reinterpret_cast<uint64_t *>(lds);
+        mv = xv + sk;
+        xi = reinterpret_cast<uint32_t *>(mv + bcap);
+        mi = xi + sk;
+        reset(width);
+    }
+    __device__ __forceinline__ void reset(int width) {
+        b = width;
+        side = K::empty();
+        bound = K::empty();
+        ns = nM = cursor = 0;
+        im = cbase = -1;
+    }
+
+    // B <- one key, held by a lane where `mine`
+    __device__ __forceinline__ void start(const K &k, bool mine) {
+        const K x = k.lane(__ffsll((long long)__ballot(mine)) - 1);
+        if (lane_id() == 0) side = x;
+        ns = 1;
+        if (!wide()) bound = side.lane(b - 1);
+    }
+
+    // entries of main below k (per lane); three probes a round
+    __device__ __forceinline__ int lower_bound(const K &k) const {
+        int pos = 0, st = 1;
+        while (4 * st <= nM) st *= 4;
+        for (; st > 0; st >>= 2) {
+            int c = 0;
+#pragma unroll
+            for (int j = 1; j <= 3; ++j) {
+                const int i = pos + j * st - 1;
+                const bool below = main_at(min(i, nM - 1)).less(k); // (read past no branch)
+                c += (int)below & (int)(i < nM);
+            }
+            pos += c * st;
+        }
+        return pos;
+    }
+
+    // side into main.  Side key j ends at (main keys below it) + j; a bit
+    // array of those places tells every other place which entry of main it
+    // takes.  Places are filled from the top down, 256 at a time, all reads
+    // before the writes: a place takes an entry at or below itself.
+    __device__ void merge_side() {
+        if (ns == 0) return;
+        const int lane = lane_id();
+        wave_sync();
+        const int np = lane < ns ? lower_bound(side) + lane : 1 << 30;
+        const int total = min(b, nM + ns), words = (total + 63) >> 6;
+        for (int w = lane; w < words; w += 64) xv[w] = 0ull;
+        wave_sync();
+        if (np < total) atomicOr(reinterpret_cast<unsigned long long *>(xv + (np >> 6)), 1ull << (np & 63));
+        wave_sync();
+        const int first = __builtin_amdgcn_readfirstlane(np) >> 6; // places below it keep their keys
+        for (int top = words - 1; top >= first; top -= 4) {
+            K k[4];
+            int to[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int w = top - j;
+                to[j] = -1;
+                if (w < first) continue;
+                const uint64_t taken = xv[w];
+                const int o = 64 * w + lane;
+                const int before = __popcll(__ballot(np < 64 * w)) + mbcnt(taken);
+                if (!((taken >> lane) & 1ull) && o < total) {
+                    to[j] = o;
+                    k[j] = main_at(o - before);
+                }
+            }
+            wave_sync();
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (to[j] >= 0) main_set(to[j], k[j]);
+            wave_sync();
+        }
+        if (np < total) main_set(np, side);
+        // the first unvisited side key may now lie before the cursor
+        const unsigned long long u = __ballot(np < total && !side.visited());
+        if (u) cursor = min(cursor, (int)__builtin_amdgcn_readlane(np, __ffsll((long long)u) - 1));
+        nM = total;
+        ns = 0;
+        im = cbase = -1;
+        side = K::empty();
+        wave_sync();
+        if (nM == b) bound = main_at(b - 1).lane(0);
+    }
+
+    // the lanes of `t`, four at a time (one after the other, each step of the
+    // loop would wait for the scalar unit): j is the lane (64: none left), x
+    // its key (empty)
+    template <typename F> static __device__ __forceinline__ void for_lanes(unsigned long long t, const K &c, F f) {
+        while (t) {
+            int j[4];
+            K x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                j[i] = t ? __ffsll((long long)t) - 1 : 64;
+                t &= t - 1; // 0 stays 0
+                x[i] = pick(j[i] < 64, c.lane(j[i] & 63), K::empty());
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f(j[i], x[i]);
+        }
+    }
+
+    // add the lanes' new keys `c` where valid.  `dedupe`: keys of B may come
+    // back (a cache forgot them) and are dropped; `repeats`: the lanes may
+    // hold one key several times.
+    __device__ void insert(K c, bool valid, bool dedupe, bool repeats = false) {
+        const int lane = lane_id();
+        unsigned long long m = __ballot(valid && c.less(bound));
+        if (!m) return;
+        if (dedupe && nM > 0) {
+            bool again = false; // in main, visited or not
+            if ((m >> lane) & 1ull) {
+                const int lb = lower_bound(c);
+                again = (int)main_at(min(lb, nM - 1)).same(c) & (int)(lb < nM);
+            }
+            m &= ~__ballot(again);
+        }
+        if (dedupe && (ns > 0 || repeats)) {
+            const unsigned long long t = m;
+            for_lanes(t, c, [&](int j, const K &x) {
+                const unsigned long long bit = j < 64 ? 1ull << j : 0ull;
+                if (__ballot(side.same(x))) m &= ~bit;
+                else if (repeats && (m & bit)) m &= ~(__ballot(c.same(x)) & ~bit);
+            });
+        }
+        if (wide() && ns + __popcll(m) > 64) {
+            merge_side();
+            m &= __ballot(c.less(bound));
+        }
+        const int k = __popcll(m);
+        if (k == 0) return;
+        c = pick((m >> lane) & 1ull, c, K::empty());
+        const int total = wide() ? ns + k : min(b, ns + k);
+        if (k > 24) {
+            key_sort_steps<64>(c, false, lane);        // descending
+            side = pick(c.less(side), c, side);        // the 64 smallest of both
+            key_merge_steps<64, 32>(side, true, lane); // ascending
+        } else {
+            int np = 64, up = 0; // the new key's lane; the old key's way up
+            for_lanes(m, c, [&](int j, const K &x) {
+                const unsigned long long below = __ballot(side.less(x));
+                const int pos = __popcll(below) + __popcll(__ballot(c.less(x)));
+                np = lane == j ? pos : np;
+                up += (below >> lane) & 1ull ? 0 : 1; // (the empty key moves no key)
+            });
+            wave_sync();
+            if (lane < ns && lane + up < 64) scratch_set(lane + up, side);
+            if (np < 64) scratch_set(np, c);
+            wave_sync();
+            side = scratch_at(lane);
+            wave_sync();
+        }
+        ns = total;
+        side = pick(lane < ns, side, K::empty());
+        if (!wide()) bound = side.lane(b - 1);
+    }
+
+    // the smallest key of B
+    __device__ __forceinline__ K best() const {
+        const K s = side.lane(0);
+        if (!wide() || nM == 0) return s;
+        const K h = main_at(0).lane(0);
+        return pick(s.less(h), s, h);
+    }
+
+    // p*: the first unvisited key of B.  Returns false if there is none.
+    // `at`: its place, for visit(): a lane, or 64 + an entry of main.
+    __device__ bool next(K &p, int &at) {
+        const int lane = lane_id();
+        const unsigned long long u = __ballot(!side.visited());
+        const int js = u ? __ffsll((long long)u) - 1 : 0;
+        if (!wide()) {
+            if (!u) return false;
+            p = side.lane(js);
+            at = js;
+            return true;
+        }
+        if (im < 0) {
+            im = nM;
+            for (int base = cursor & ~63; base < nM; base += 64) {
+                const int i = base + lane;
+                if (cbase != base) {
+                    ck = i < nM ? main_at(i) : K::empty();
+                    cbase = base;
+                }
+                const unsigned long long m = __ballot(i >= cursor && !ck.visited());
+                if (m) {
+                    const int j = __ffsll((long long)m) - 1;
+                    im = base + j;
+                    km = ck.lane(j);
+                    break;
+                }
+            }
+            cursor = im;
+        }
+        const bool has_m = im < nM;
+        if (!has_m && !u) return false;
+        const K ks = side.lane(js);
+        const bool take_s = u && (!has_m || ks.less(km));
+        // is the smaller one's rank below b?  (the keys before a key of rank
+        // below b have ranks below b too)
+        bool in_b = nM + ns <= b;
+        if (!in_b && has_m) in_b = im + __popcll(__ballot(side.less(km))) < b;
+        if (!in_b && take_s) {
+            const int t = b - 1 - js; // js + (main keys below ks) < b
+            in_b = t >= nM || !main_at(t).lane(0).less(ks);
+        }
+        if (!in_b) return false;
+        p = pick(take_s, ks, km);
+        at = take_s ? js : 64 + im;
+        return true;
+    }
+
+    __device__ __forceinline__ void visit(int at) {
+        const int lane = lane_id();
+        if (at < 64) {
+            if (lane == at) side.visit();
+        } else {
+            if (64 + cbase + lane == at) {
+                ck.visit();
+                main_set(at - 64, ck);
+            }
+            cursor = at - 64 + 1;
+            im = -1;
+        }
+    }
+
+    // B in order in main; returns its size
+    __device__ int settle() {
+        if (wide()) {
+            merge_side();
+            return nM;
+        }
+        const int lane = lane_id();
+        wave_sync();
+        if (lane < ns) main_set(lane, side);
+        wave_sync();
+        return ns;
+    }
+
+    // B from n stored keys (stored(i) for i < n, in order)
+    template <typename F> __device__ void restore(int n, F stored) {
+        const int lane = lane_id();
+        if (!wide()) {
+            side = lane < n ? stored(lane) : K::empty();
+            ns = n;
+            bound = side.lane(b - 1);
+            return;
+        }
+        wave_sync();
+        for (int i = lane; i < n; i += 64) main_set(i, stored(i));
+        wave_sync();
+        nM = n;
+        if (nM == b) bound = main_at(b - 1).lane(0);
+    }
+};
+
+// LDS of one wave: scratch (which also holds the ids of a visit's candidates
+// until their keys are made), main, the seen cache
+template <typename D>
+__host__ __device__ inline int32_t wave_lds_bytes(int32_t bcap, int32_t cs) {
+    return (((bcap + WaveBeam<D>::scratch_keys(bcap)) * (sizeof(D) == 8 ? 12 : 8) + 15) & ~15) + cs * 4;
+}
+
+// --------------------------------------------------------------------------
 // beam kernel: Algorithm 1 (+ Algorithm 5), then Algorithm 6's decision
 // --------------------------------------------------------------------------
 
@@ -682,44 +1224,31 @@ struct BeamArgs {
     int8_t *probe_f;
 };
 
-template <typename D>
-__host__ __device__ inline int32_t beam_lds_bytes(int32_t bcap, int32_t cs) {
-    // the beam kernel merges in place: one copy of B
-    auto al = [](int64_t x) { return (int32_t)((x + 15) & ~15ll); };
-    return al((int64_t)bcap * sizeof(D)) + al(64 * sizeof(D)) + al((int64_t)bcap * 4) +
-           al(64 * 4) + al((int64_t)cs * 4);
-}
-
-// the doubling kernel double-buffers its beam
-template <typename D>
-__host__ __device__ inline int32_t doubling_lds_bytes(int32_t bcap, int32_t cs) {
-    auto al = [](int64_t x) { return (int32_t)((x + 15) & ~15ll); };
-    return al((int64_t)bcap * sizeof(D)) * 2 + al(64 * sizeof(D)) + al((int64_t)bcap * 4) * 2 +
-           al(64 * 4) + al((int64_t)cs * 4);
-}
+// Waves per SIMD that the beam kernel's registers are held to: integer rows
+// of up to 1 KB need about 120 registers, so four waves fit; the others hold
+// more of a row at once (1M x 96 float32, 2,500 queries: 0.280 ms at three
+// waves, 0.307 ms at two; at four they spill, 0.92 ms).
+template <int DTYPE, int CPL> constexpr int beam_waves() { return !dfloat(DTYPE) && CPL == 1 ? 4 : 3; }
 
 template <int DTYPE, int CPL, int G>
-__global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
+__global__ __launch_bounds__(512, (beam_waves<DTYPE, CPL>())) void k_beam(BeamArgs a) {
     using D = typename DistOf<DTYPE>::T;
     using O = typename DistOf<DTYPE>::O;
+    using K = BeamKey<D>;
     extern __shared__ __align__(16) uint8_t smem[];
     const int lane = lane_id();
-    const int wid = threadIdx.x >> 6;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t *my = smem + (size_t)wid * a.lds_per_wave;
-    auto al = [](int64_t x) { return (int64_t)((x + 15) & ~15ll); };
-    const int bcap = a.bcap;
     const int cs = a.cfg.cache_slots;
-    D *const bd = (D *)my;
-    D *cd = (D *)(my + al((int64_t)bcap * sizeof(D)));
-    uint8_t *p2 = my + al((int64_t)bcap * sizeof(D)) + al(64 * sizeof(D));
-    uint32_t *const bi = (uint32_t *)p2;
-    uint32_t *ci = (uint32_t *)(p2 + al((int64_t)bcap * 4));
-    uint32_t *htab = (uint32_t *)(p2 + al((int64_t)bcap * 4) + al(64 * 4));
-    const uint32_t cs_mask = (uint32_t)cs - 1u;
+    const int cs_shift = 32 - (31 - __clz(cs >> 3));
+    uint32_t *const ci = (uint32_t *)my; // the beam's scratch
+    uint32_t *const htab = (uint32_t *)(my + a.lds_per_wave - 4 * cs);
     const DevIndex &ix = a.ix;
     const SearchCfg &cfg = a.cfg;
     const int R = ix.R;
     const int b = cfg.beam;
+    WaveBeam<D> B;
+    B.init(my, a.bcap, b);
 
     // The work queue is striped over QSTRIPES counters on separate lines (one
     // counter would serialize every fetch): stripe s hands out work items s,
@@ -727,110 +1256,101 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
     // moves to the next one when a stripe runs dry; a stripe never refills, so
     // a wave that has passed every stripe is done.  A relaxed load skips
     // stripes already seen dry without an atomic.
-    int stripe = (int)(((int64_t)blockIdx.x * (blockDim.x >> 6) + wid) % QSTRIPES);
+    int stripe = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * (blockDim.x >> 6) + wid) % QSTRIPES));
     int dry = 0;
     for (;;) {
-        int64_t wk = -1;
+        int32_t wk = -1; // (wave-uniform: held, like all that follows from it, in scalar registers)
         while (dry < QSTRIPES) {
-            int64_t k = -1;
+            int32_t k = -1;
             if (lane == 0) {
                 unsigned long long *c = &a.sb.counters[CTR_QSTRIPE + stripe * CTR_STRIDE];
                 const unsigned long long seen =
                     __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((int64_t)stripe + (int64_t)seen * QSTRIPES < a.nwork) k = (int64_t)atomicAdd(c, 1ull);
+                if ((int64_t)stripe + (int64_t)seen * QSTRIPES < a.nwork) k = (int32_t)atomicAdd(c, 1ull);
             }
-            k = __shfl(k, 0);
-            if (k >= 0 && (int64_t)stripe + k * QSTRIPES < a.nwork) {
-                wk = (int64_t)stripe + k * QSTRIPES;
+            k = __builtin_amdgcn_readfirstlane(k);
+            if (k >= 0 && (int64_t)stripe + (int64_t)k * QSTRIPES < a.nwork) {
+                wk = stripe + k * QSTRIPES;
                 break;
             }
             stripe = stripe + 1 == QSTRIPES ? 0 : stripe + 1;
             ++dry;
         }
         if (wk < 0) break;
-        const int64_t q = a.qlist ? (int64_t)a.qlist[wk] : wk;
+        const int64_t q = a.qlist ? __builtin_amdgcn_readfirstlane(a.qlist[wk]) : wk;
 
         const QThresh th = a.sb.qth[q];
         QueryRegs<DTYPE, CPL, G> qr;
         qr.load(a.sb.qpad + (size_t)q * qrow_stride<DTYPE>(ix), ix);
 
-        for (int i = lane; i < cs; i += 64) htab[i] = RR_EMPTY32;
+        for (int i = lane; i < cs / 4; i += 64)
+            reinterpret_cast<uint4 *>(htab)[i] = make_uint4(RR_EMPTY32, RR_EMPTY32, RR_EMPTY32, RR_EMPTY32);
         wave_sync();
 
         bool ovf = false;
-        int nB = 1;
+        bool dedupe = false; // the cache may have forgotten points of B
         int visits = 0, evals = 1;
         int edges = 0; // adjacency entries read by the visits (sum of out-degrees)
-        int cursor = 0;
         bool es_fired = false;
+        B.reset(b);
         if (a.state && (a.state[q].flags & BS_STARTED)) {
             // resume: B as it was stored; the visited cache starts empty,
             // which is exact because the cache may forget ids
             const BeamState bs = a.state[q];
-            nB = bs.nB;
-            visits = bs.visits;
-            evals = bs.evals;
-            edges = bs.edges;
-            cursor = bs.cursor;
+            visits = __builtin_amdgcn_readfirstlane(bs.visits);
+            evals = __builtin_amdgcn_readfirstlane(bs.evals);
+            edges = __builtin_amdgcn_readfirstlane(bs.edges);
             ovf = lane == 0 && (bs.flags & BS_OVF);
-            const D *sd = (const D *)a.st_d + (size_t)q * bcap;
-            const uint32_t *si = a.st_i + (size_t)q * bcap;
-            for (int i = lane; i < nB; i += 64) {
-                bd[i] = sd[i];
-                bi[i] = si[i];
-            }
-            wave_sync();
+            dedupe = true;
+            const D *sd = (const D *)a.st_d + (size_t)q * a.bcap;
+            const uint32_t *si = a.st_i + (size_t)q * a.bcap;
+            B.restore(__builtin_amdgcn_readfirstlane(bs.nB), [&](int i) {
+                K k = K::make(sd[i], si[i] & RR_IDMASK);
+                if (si[i] & RR_VIS) k.visit();
+                return k;
+            });
         } else {
             // B <- S = {entry}
             if (lane == 0) {
                 ci[0] = (uint32_t)ix.entry;
-                seen_insert(htab, cs_mask, (uint32_t)ix.entry, ovf);
+                seen_insert(htab, cs_shift, (uint32_t)ix.entry, ovf);
             }
             wave_sync();
-            eval_rows<DTYPE, CPL, G>(ix, qr, ci, cd, 1);
-            if (lane == 0) {
-                bd[0] = cd[0];
-                bi[0] = (uint32_t)ix.entry;
-                if (a.probe_m) {
-                    const double nan = __builtin_nan("");
-                    a.probe_m[4 * q] = nan;
-                    a.probe_m[4 * q + 1] = nan;
-                    a.probe_m[4 * q + 2] = nan;
-                    a.probe_m[4 * q + 3] = (double)cd[0] - (double)ix.key_off;
-                    a.probe_f[2 * q] = 0;
-                    a.probe_f[2 * q + 1] = 0;
-                }
+            int c = 0;
+            const D d0 = eval64<DTYPE, CPL, G>(ix, qr, ci, 1, c);
+            B.start(K::make(d0, (uint32_t)ix.entry), c == 0);
+            if (a.probe_m && c == 0) {
+                const double nan = __builtin_nan("");
+                a.probe_m[4 * q] = nan;
+                a.probe_m[4 * q + 1] = nan;
+                a.probe_m[4 * q + 2] = nan;
+                a.probe_m[4 * q + 3] = (double)d0 - (double)ix.key_off;
+                a.probe_f[2 * q] = 0;
+                a.probe_f[2 * q + 1] = 0;
             }
-            wave_sync();
         }
         int steps = 0;
         bool suspend = false;
 
         for (;;) {
-            // p* = first unvisited entry of the sorted beam at or after cursor
-            int ip = -1;
-            for (int base = cursor & ~63; base < nB; base += 64) {
-                const int i = base + lane;
-                const bool unv = i >= cursor && i < nB && !(bi[i] & RR_VIS);
-                const unsigned long long m = __ballot(unv);
-                if (m) {
-                    ip = base + __ffsll((long long)m) - 1;
-                    break;
+            K p;
+            int at;
+            if (!B.next(p, at)) break;
+            if (a.probe_m && visits == a.probe_step) {
+                const int nB = B.settle();
+                if (lane == 0) {
+                    const double ko = (double)ix.key_off;
+                    a.probe_m[4 * q] = (double)p.dist() - ko;
+                    a.probe_m[4 * q + 1] = (double)B.main_at(0).dist() - ko;
+                    a.probe_m[4 * q + 2] = nB >= 10 ? (double)B.main_at(9).dist() - ko : __builtin_inf();
+                    a.probe_f[2 * q] = 1;
+                    a.probe_f[2 * q + 1] = in_range<D>(B.main_at(0).dist(), th) ? 1 : 0;
                 }
-            }
-            if (ip < 0) break;
-            const D dp = bd[ip];
-            if (a.probe_m && visits == a.probe_step && lane == 0) {
-                const double ko = (double)ix.key_off;
-                a.probe_m[4 * q] = (double)dp - ko;
-                a.probe_m[4 * q + 1] = (double)bd[0] - ko;
-                a.probe_m[4 * q + 2] = nB >= 10 ? (double)bd[9] - ko : __builtin_inf();
-                a.probe_f[2 * q] = 1;
-                a.probe_f[2 * q + 1] = in_range<D>(bd[0], th) ? 1 : 0;
+                B.next(p, at); // settling may have moved p*
             }
             // Algorithm 5: min_B d > r, v >= vl, d(p*) > esr
-            if (cfg.es_enable && visits >= cfg.vl && !in_range<D>(bd[0], th) &&
-                beyond_esr<D>(dp, th)) {
+            if (cfg.es_enable && visits >= cfg.vl && !in_range<D>(B.best().dist(), th) &&
+                beyond_esr<D>(p.dist(), th)) {
                 es_fired = true;
                 break;
             }
@@ -839,97 +1359,38 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
                 break;
             }
             ++steps;
-            const uint32_t p = bi[ip] & RR_IDMASK;
-            wave_sync();
-            if (lane == 0) bi[ip] = p | RR_VIS;
-            ++visits;
             // N_out(p*), drop ids already evaluated
-            int32_t f = -1;
-            if (lane < R) f = ix.adj[(size_t)p * (size_t)R + lane];
+            int32_t f = ix.adj[(uint64_t)p.id() * (uint32_t)R + max(0, min(lane, R - 1))];
+            if (lane >= R) f = -1;
+            B.visit(at);
+            ++visits;
             edges += __popcll(__ballot(f >= 0));
             bool cand = false;
-            if (f >= 0) cand = !seen_insert(htab, cs_mask, (uint32_t)f, ovf);
+            if (f >= 0) cand = !seen_insert(htab, cs_shift, (uint32_t)f, ovf);
             const unsigned long long cm = __ballot(cand);
             const int k = __popcll(cm);
+            if (k == 0) continue;
             if (cand) ci[mbcnt(cm)] = (uint32_t)f;
             wave_sync();
             evals += k;
-            if (k == 0) {
-                cursor = ip + 1;
-                continue;
-            }
-            eval_rows<DTYPE, CPL, G>(ix, qr, ci, cd, k);
-            D myd = dmax<D>();
-            uint32_t myi = RR_EMPTY32;
-            if (lane < k) {
-                myd = cd[lane];
-                myi = ci[lane];
-            }
-            wave_sort(myd, myi);
-            // de-duplicate against B (a forgotten id may be re-evaluated)
-            int lb = 0;
-            bool keep = false;
-            if (lane < k) {
-                lb = lower_bound_key(bd, bi, nB, myd, myi);
-                keep = !(lb < nB && bd[lb] == myd && (bi[lb] & RR_IDMASK) == myi);
-            }
-            const unsigned long long km = __ballot(keep);
-            const int k2 = __popcll(km);
-            const int r2 = mbcnt(km);
+            int c = 0;
+            const D d = eval64<DTYPE, CPL, G>(ix, qr, ci, k, c);
+            // a key of B can only come back once the cache has forgotten one
+            dedupe = dedupe || __ballot(ovf) != 0ull;
+            const uint32_t id = ci[min(c, 63)];
             wave_sync();
-            if (keep) {
-                cd[r2] = myd;
-                ci[r2] = myi;
-            }
-            wave_sync();
-            // merge in place: B entry i moves to i + #(survivors < B[i]) >= i,
-            // survivor j to j + lb_j.  Chunks of 64 entries are moved from the
-            // top down: a chunk's entries land at or above its own start, where
-            // every entry was read already, so nothing unread is overwritten.
-            const int nB2 = min(b, nB + k2);
-            int ipnew = ip;
-            // entries below the first survivor's position keep their place
-            const int lb_first = k2 > 0 ? __shfl(lb, __ffsll((long long)km) - 1) : nB;
-            for (int base = (nB - 1) & ~63; base >= (lb_first & ~63); base -= 64) {
-                const int i = base + lane;
-                D di = D(0);
-                uint32_t ii = 0u;
-                int np = 1 << 30;
-                if (i < nB) {
-                    di = bd[i];
-                    ii = bi[i];
-                    np = i + lower_bound_key(cd, ci, k2, di, ii & RR_IDMASK);
-                }
-                wave_sync();
-                if (np < b) {
-                    bd[np] = di;
-                    bi[np] = ii;
-                }
-                if (i == ip) ipnew = np;
-            }
-            wave_sync();
-            ipnew = __shfl(ipnew, ip & 63);
-            int firstnew = 1 << 30;
-            if (keep) {
-                const int np = r2 + lb;
-                if (np < b) {
-                    bd[np] = myd;
-                    bi[np] = myi;
-                }
-                if (r2 == 0) firstnew = np;
-            }
-            if (k2 > 0) firstnew = __shfl(firstnew, __ffsll((long long)km) - 1);
-            wave_sync();
-            nB = nB2;
-            cursor = min(ipnew + 1, firstnew);
+            B.insert(K::make(d, id), c < k, dedupe);
         }
 
+        // B in order in LDS
+        const int nB = B.settle();
         if (suspend) {
-            D *sd = (D *)a.st_d + (size_t)q * bcap;
-            uint32_t *si = a.st_i + (size_t)q * bcap;
+            D *sd = (D *)a.st_d + (size_t)q * a.bcap;
+            uint32_t *si = a.st_i + (size_t)q * a.bcap;
             for (int i = lane; i < nB; i += 64) {
-                sd[i] = bd[i];
-                si[i] = bi[i];
+                const K k = B.main_at(i);
+                sd[i] = k.dist();
+                si[i] = k.id() | (k.visited() ? RR_VIS : 0u);
             }
             const bool any_ovf = __ballot(ovf) != 0ull;
             if (lane == 0) {
@@ -937,7 +1398,6 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
                 bs.nB = nB;
                 bs.visits = visits;
                 bs.evals = evals;
-                bs.cursor = cursor;
                 bs.flags = BS_STARTED | (any_ovf ? BS_OVF : 0);
                 bs.edges = edges;
                 a.state[q] = bs;
@@ -953,21 +1413,21 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
         if constexpr (dapprox(DTYPE)) {
             for (int base = 0; base < nB; base += 64) {
                 const int i = base + lane;
-                const int c = __popcll(__ballot(i < nB && bd[i] <= th.hi));
+                const int c = __popcll(__ballot(i < nB && B.main_at(i).dist() <= th.hi));
                 cH += c;
                 if (c < 64) break;
             }
             for (int base = 0; base < cH; base += 64) {
                 const int i = base + lane;
                 bool inr = false;
-                if (i < cH) inr = exact_dist_f32<dip(DTYPE)>(ix, bi[i] & RR_IDMASK, qr.row) <= th.r;
+                if (i < cH) inr = exact_dist_f32<dip(DTYPE)>(ix, B.main_at(i).id(), qr.row) <= th.r;
                 cN += __popcll(__ballot(inr));
-                nband += __popcll(__ballot(i < cH && bd[i] > th.lo));
+                nband += __popcll(__ballot(i < cH && B.main_at(i).dist() > th.lo));
             }
         } else {
             for (int base = 0; base < nB; base += 64) {
                 const int i = base + lane;
-                const bool inr = i < nB && in_range<D>(bd[i], th);
+                const bool inr = i < nB && in_range<D>(B.main_at(i).dist(), th);
                 const int c = __popcll(__ballot(inr));
                 cN += c;
                 if (c < 64) break;
@@ -1003,7 +1463,7 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
         if (!as_task) {
             int64_t off = 0;
             if (lane == 0 && cN > 0) off = (int64_t)atomicAdd(&a.sb.counters[CTR_ARENA], (unsigned long long)cN);
-            off = __shfl(off, 0);
+            off = uniform64(off);
             if (cN > 0 && off + cN > a.sb.arena_cap) {
                 st.truncated = 1;
                 st.count = 0;
@@ -1011,8 +1471,8 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
             } else {
                 O *ad = (O *)a.sb.arena_dists;
                 for (int i = lane; i < cN; i += 64) {
-                    a.sb.arena_ids[off + i] = (int32_t)(bi[i] & RR_IDMASK);
-                    ad[off + i] = (O)bd[i];
+                    a.sb.arena_ids[off + i] = (int32_t)B.main_at(i).id();
+                    ad[off + i] = (O)B.main_at(i).dist();
                 }
             }
             if (lane == 0) {
@@ -1024,7 +1484,7 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
             // `expand`; otherwise it is just sorted and emitted)
             int64_t t = 0;
             if (lane == 0) t = (int64_t)atomicAdd(&a.sb.counters[CTR_TASKS], 1ull);
-            t = __shfl(t, 0);
+            t = uniform64(t);
             if (expand) tset_clear(a.sb, t);
             bool full = false;
             int written = 0;
@@ -1035,7 +1495,7 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
                     double dx = 0.0;
                     bool inr = false;
                     if (i < cH) {
-                        dx = exact_dist_f32<dip(DTYPE)>(ix, bi[i] & RR_IDMASK, qr.row);
+                        dx = exact_dist_f32<dip(DTYPE)>(ix, B.main_at(i).id(), qr.row);
                         inr = dx <= th.r;
                     }
                     const unsigned long long im = __ballot(inr);
@@ -1044,11 +1504,11 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
                     int64_t off = 0;
                     if (lane == 0)
                         off = (int64_t)(atomicAdd(&a.sb.level_cnt[0], (unsigned long long)m));
-                    off = __shfl(off, 0);
+                    off = uniform64(off);
                     const int64_t o = off + mbcnt(im);
                     const bool wr = inr && o < a.sb.item_cap;
                     if (wr) {
-                        const uint32_t id = bi[i] & RR_IDMASK;
+                        const uint32_t id = B.main_at(i).id();
                         a.sb.item_key[o] = ((unsigned long long)(uint32_t)t << 32) | id;
                         idist[o] = dx;
                     }
@@ -1060,16 +1520,16 @@ __global__ __launch_bounds__(512) void k_beam(BeamArgs a) {
                 int64_t off = 0;
                 if (lane == 0)
                     off = (int64_t)(atomicAdd(&a.sb.level_cnt[0], (unsigned long long)cN));
-                off = __shfl(off, 0);
+                off = uniform64(off);
                 for (int i = lane; i < cN; i += 64) {
                     const int64_t o = off + i;
                     if (o >= a.sb.item_cap) {
                         full = true;
                         continue;
                     }
-                    const uint32_t id = bi[i] & RR_IDMASK;
+                    const uint32_t id = B.main_at(i).id();
                     a.sb.item_key[o] = ((unsigned long long)(uint32_t)t << 32) | id;
-                    idist[o] = (O)bd[i];
+                    idist[o] = (O)B.main_at(i).dist();
                 }
                 written = (int)max((int64_t)0, min((int64_t)cN, a.sb.item_cap - off));
             }
@@ -1135,22 +1595,18 @@ template <int DTYPE, int CPL, int G>
 __global__ __launch_bounds__(512) void k_doubling(DoublingArgs a) {
     using D = typename DistOf<DTYPE>::T;
     using O = typename DistOf<DTYPE>::O;
+    using K = BeamKey<D>;
     extern __shared__ __align__(16) uint8_t smem[];
     const int lane = lane_id();
-    const int wid = threadIdx.x >> 6;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t *my = smem + (size_t)wid * a.lds_per_wave;
-    auto al = [](int64_t x) { return (int64_t)((x + 15) & ~15ll); };
     const int bcap = a.bcap;
     const int cs = a.cfg.cache_slots;
-    D *const bdA = (D *)my;
-    D *const bdB = (D *)(my + al((int64_t)bcap * sizeof(D)));
-    D *const cd = (D *)(my + 2 * al((int64_t)bcap * sizeof(D)));
-    uint8_t *p2 = my + 2 * al((int64_t)bcap * sizeof(D)) + al(64 * sizeof(D));
-    uint32_t *const biA = (uint32_t *)p2;
-    uint32_t *const biB = (uint32_t *)(p2 + al((int64_t)bcap * 4));
-    uint32_t *const ci = (uint32_t *)(p2 + 2 * al((int64_t)bcap * 4));
-    uint32_t *const htab = (uint32_t *)(p2 + 2 * al((int64_t)bcap * 4) + al(64 * 4));
-    const uint32_t cs_mask = (uint32_t)cs - 1u;
+    const int cs_shift = 32 - (31 - __clz(cs >> 3));
+    uint32_t *const ci = (uint32_t *)my; // the beam's scratch
+    uint32_t *const htab = (uint32_t *)(my + a.lds_per_wave - 4 * cs);
+    WaveBeam<D> B;
+    B.init(my, bcap, a.cfg.beam);
     const DevIndex &ix = a.ix;
     const SearchCfg &cfg = a.cfg;
     const int R = ix.R;
@@ -1159,185 +1615,100 @@ __global__ __launch_bounds__(512) void k_doubling(DoublingArgs a) {
     uint32_t *const si = (uint32_t *)(sd + a.s_cap);
 
     for (;;) {
-        int64_t q = 0;
-        if (lane == 0) q = (int64_t)atomicAdd(&a.sb.counters[CTR_QUEUE], 1ull);
-        q = __shfl(q, 0);
+        int32_t qi = 0; // at most nq + the number of waves
+        if (lane == 0) qi = (int32_t)atomicAdd(&a.sb.counters[CTR_QUEUE], 1ull);
+        const int64_t q = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(qi);
         if (q >= a.nq) break;
 
         const QThresh th = a.sb.qth[q];
         QueryRegs<DTYPE, CPL, G> qr;
         qr.load(a.sb.qpad + (size_t)q * qrow_stride<DTYPE>(ix), ix);
 
-        D *bd = bdA, *bdo = bdB;
-        uint32_t *bi = biA, *bio = biB;
-        int nB = 0;
         bool ovf = false, trunc = false, es_any = false;
         int b = cfg.beam, rounds = 0, cN = 0;
         int64_t ns = 0, visits_all = 0, evals_all = 0, edges_all = 0;
 
-        // merge the k (<= 64) candidates held by the lanes into B, trimmed to
-        // b; candidates equal to a key of B or to another candidate are
-        // dropped.  Returns the new position of B[ip] and of the first kept
-        // candidate (for the scan cursor).
-        auto merge = [&](D myd, uint32_t myi, int k, int ip, int &ipnew, int &firstnew) {
-            wave_sort(myd, myi);
-            const D pd = __shfl_up(myd, 1);
-            const uint32_t pi = __shfl_up(myi, 1);
-            int lb = 0;
-            bool keep = false;
-            if (lane < k) {
-                lb = lower_bound_key(bd, bi, nB, myd, myi);
-                keep = !(lb < nB && bd[lb] == myd && (bi[lb] & RR_IDMASK) == myi) &&
-                       !(lane > 0 && pd == myd && pi == myi);
-            }
-            const unsigned long long km = __ballot(keep);
-            const int k2 = __popcll(km);
-            const int r2 = mbcnt(km);
-            wave_sync();
-            if (keep) {
-                cd[r2] = myd;
-                ci[r2] = myi;
-            }
-            wave_sync();
-            const int nB2 = min(b, nB + k2);
-            int ipn = ip;
-            for (int i = lane; i < nB; i += 64) {
-                const D di = bd[i];
-                const uint32_t ii = bi[i];
-                const int np = i + lower_bound_key(cd, ci, k2, di, ii & RR_IDMASK);
-                if (np < b) {
-                    bdo[np] = di;
-                    bio[np] = ii;
-                }
-                if (i == ip) ipn = np;
-            }
-            ipnew = ip >= 0 ? __shfl(ipn, ip & 63) : -1;
-            int fn = 1 << 30;
-            if (keep) {
-                const int np = r2 + lb;
-                if (np < b) {
-                    bdo[np] = myd;
-                    bio[np] = myi;
-                }
-                if (r2 == 0) fn = np;
-            }
-            firstnew = k2 > 0 ? __shfl(fn, __ffsll((long long)km) - 1) : (1 << 30);
-            wave_sync();
-            D *td = bd;
-            bd = bdo;
-            bdo = td;
-            uint32_t *ti = bi;
-            bi = bio;
-            bio = ti;
-            nB = nB2;
-        };
-
         for (;;) {
-            for (int i = lane; i < cs; i += 64) htab[i] = RR_EMPTY32;
+            for (int i = lane; i < cs / 4; i += 64)
+                reinterpret_cast<uint4 *>(htab)[i] = make_uint4(RR_EMPTY32, RR_EMPTY32, RR_EMPTY32, RR_EMPTY32);
             wave_sync();
-            nB = 0;
+            B.reset(b);
             int evals = 0;
+            // the cache starts empty: points of S come back as neighbours
+            bool dedupe = rounds > 0;
             if (rounds == 0) {
                 // B <- S = {entry}
                 if (lane == 0) {
                     ci[0] = (uint32_t)ix.entry;
-                    seen_insert(htab, cs_mask, (uint32_t)ix.entry, ovf);
+                    seen_insert(htab, cs_shift, (uint32_t)ix.entry, ovf);
                 }
                 wave_sync();
-                eval_rows<DTYPE, CPL, G>(ix, qr, ci, cd, 1);
-                if (lane == 0) {
-                    bd[0] = cd[0];
-                    bi[0] = (uint32_t)ix.entry;
-                }
-                wave_sync();
-                nB = 1;
+                int c = 0;
+                const D d0 = eval64<DTYPE, CPL, G>(ix, qr, ci, 1, c);
+                B.start(K::make(d0, (uint32_t)ix.entry), c == 0);
                 evals = 1;
             } else {
                 // B <- the b best keys of S.  S was written by lane 0; the
                 // stores are completed, then read at L2 (agent-scope loads
                 // bypass the per-CU cache, which may hold an older query's S)
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                int ipn, fn;
                 for (int64_t c0 = 0; c0 < ns; c0 += 64) {
-                    const int k = (int)min((int64_t)64, ns - c0);
-                    D myd = dmax<D>();
-                    uint32_t myi = RR_EMPTY32;
-                    if (lane < k) {
-                        myd = load_l2(sd + c0 + lane);
-                        myi = load_l2(si + c0 + lane);
-                    }
-                    merge(myd, myi, k, -1, ipn, fn);
+                    K k = K::empty();
+                    if (c0 + lane < ns) k = K::make(load_l2(sd + c0 + lane), load_l2(si + c0 + lane));
+                    B.insert(k, c0 + lane < ns, true, true);
                 }
             }
-            int cursor = 0, visits = 0;
+            int visits = 0;
             bool es_fired = false;
             for (;;) {
-                int ip = -1;
-                for (int base = cursor & ~63; base < nB; base += 64) {
-                    const int i = base + lane;
-                    const bool unv = i >= cursor && i < nB && !(bi[i] & RR_VIS);
-                    const unsigned long long m = __ballot(unv);
-                    if (m) {
-                        ip = base + __ffsll((long long)m) - 1;
-                        break;
-                    }
-                }
-                if (ip < 0) break;
-                const D dp = bd[ip];
+                K p;
+                int at;
+                if (!B.next(p, at)) break;
                 // Algorithm 5 within the round: min_B d > r, v >= vl, d(p*) > esr
-                if (cfg.es_enable && visits >= cfg.vl && !in_range<D>(bd[0], th) &&
-                    beyond_esr<D>(dp, th)) {
+                if (cfg.es_enable && visits >= cfg.vl && !in_range<D>(B.best().dist(), th) &&
+                    beyond_esr<D>(p.dist(), th)) {
                     es_fired = true;
                     break;
                 }
-                const uint32_t p = bi[ip] & RR_IDMASK;
-                wave_sync();
-                if (lane == 0) bi[ip] = p | RR_VIS;
+                int32_t f = ix.adj[(uint64_t)p.id() * (uint32_t)R + max(0, min(lane, R - 1))];
+                if (lane >= R) f = -1;
+                B.visit(at);
                 ++visits;
                 // S <- S u {p*}
                 if (ns < a.s_cap) {
                     if (lane == 0) {
-                        sd[ns] = dp;
-                        si[ns] = p;
+                        sd[ns] = p.dist();
+                        si[ns] = p.id();
                     }
                     ++ns;
                 } else {
                     trunc = true;
                 }
-                int32_t f = -1;
-                if (lane < R) f = ix.adj[(size_t)p * (size_t)R + lane];
                 edges_all += __popcll(__ballot(f >= 0));
                 bool cand = false;
-                if (f >= 0) cand = !seen_insert(htab, cs_mask, (uint32_t)f, ovf);
+                if (f >= 0) cand = !seen_insert(htab, cs_shift, (uint32_t)f, ovf);
                 const unsigned long long cm = __ballot(cand);
                 const int k = __popcll(cm);
+                if (k == 0) continue;
                 if (cand) ci[mbcnt(cm)] = (uint32_t)f;
                 wave_sync();
                 evals += k;
-                if (k == 0) {
-                    cursor = ip + 1;
-                    continue;
-                }
-                eval_rows<DTYPE, CPL, G>(ix, qr, ci, cd, k);
-                D myd = dmax<D>();
-                uint32_t myi = RR_EMPTY32;
-                if (lane < k) {
-                    myd = cd[lane];
-                    myi = ci[lane];
-                }
+                int c = 0;
+                const D d = eval64<DTYPE, CPL, G>(ix, qr, ci, k, c);
+                dedupe = dedupe || __ballot(ovf) != 0ull;
+                const uint32_t id = ci[min(c, 63)];
                 wave_sync();
-                int ipnew, firstnew;
-                merge(myd, myi, k, ip, ipnew, firstnew);
-                cursor = min(ipnew + 1, firstnew);
+                B.insert(K::make(d, id), c < k, dedupe);
             }
             visits_all += visits;
             evals_all += evals;
             es_any = es_any || es_fired;
             ++rounds;
             cN = 0;
+            const int nB = B.settle();
             for (int base = 0; base < nB; base += 64) {
                 const int i = base + lane;
-                const int c = __popcll(__ballot(i < nB && in_range<D>(bd[i], th)));
+                const int c = __popcll(__ballot(i < nB && in_range<D>(B.main_at(i).dist(), th)));
                 cN += c;
                 if (c < 64) break;
             }
@@ -1372,7 +1743,7 @@ __global__ __launch_bounds__(512) void k_doubling(DoublingArgs a) {
         }
         int64_t off = 0;
         if (lane == 0 && cN > 0) off = (int64_t)atomicAdd(&a.sb.counters[CTR_ARENA], (unsigned long long)cN);
-        off = __shfl(off, 0);
+        off = uniform64(off);
         if (cN > 0 && off + cN > a.sb.arena_cap) {
             st.truncated = 1;
             st.count = 0;
@@ -1380,8 +1751,8 @@ __global__ __launch_bounds__(512) void k_doubling(DoublingArgs a) {
         } else {
             O *ad = (O *)a.sb.arena_dists;
             for (int i = lane; i < cN; i += 64) {
-                a.sb.arena_ids[off + i] = (int32_t)(bi[i] & RR_IDMASK);
-                ad[off + i] = (O)bd[i];
+                a.sb.arena_ids[off + i] = (int32_t)B.main_at(i).id();
+                ad[off + i] = (O)B.main_at(i).dist();
             }
         }
         if (lane == 0) {
@@ -2008,7 +2379,7 @@ static hipError_t run_beam(const DevIndex &ix, int64_t nq, const SearchCfg &cfg,
     a.probe_f = sl.probe_f;
     nq = a.nwork;
     a.bcap = cfg.beam;
-    a.lds_per_wave = beam_lds_bytes<D>(cfg.beam, cfg.cache_slots);
+    a.lds_per_wave = wave_lds_bytes<D>(cfg.beam, cfg.cache_slots);
     const int waves = cfg.waves;
     const size_t shmem = (size_t)a.lds_per_wave * waves;
     auto kern = k_beam<DTYPE, CPL, G>;
@@ -2064,7 +2435,7 @@ static hipError_t run_doubling(const DevIndex &ix, int64_t nq, const SearchCfg &
     a.sb = sb;
     a.nq = nq;
     a.bcap = cfg.bcap;
-    a.lds_per_wave = doubling_lds_bytes<D>(cfg.bcap, cfg.cache_slots);
+    a.lds_per_wave = wave_lds_bytes<D>(cfg.bcap, cfg.cache_slots);
     a.s_pool = (uint8_t *)s_pool;
     a.s_cap = s_cap;
     const int waves = cfg.waves;
