@@ -113,7 +113,8 @@ struct SearchBufs {
     unsigned long long *task_cnt = nullptr;   // [nq] results per task
     unsigned long long *task_evals = nullptr; // [nq]
     unsigned long long *task_rechk = nullptr; // [nq] exact rechecks in the band
-    int8_t *task_expand = nullptr;            // [nq] 1: run Algorithm 2 from the seeds
+    int8_t *task_expand = nullptr;            // [nq] 1: run Algorithm 2 from the seeds; 2: seeds expanded
+    int64_t *task_seed = nullptr;             // [nq] first of the task's seeds among the items
     int8_t *task_trunc = nullptr;             // [nq] 1: a capacity dropped some of the task's results
     const uint8_t *deg = nullptr; // [n] out-degrees (greedy visits' adjacency entries); null: not counted
     unsigned long long *task_prev = nullptr;  // [nq] task_cnt before the current level
@@ -135,6 +136,9 @@ struct SearchBufs {
     uint32_t *bm = nullptr;     // [bm_tasks][bm_words]
     int64_t bm_words = 0;       // 32-bit words per task: n bits rounded up to 128
     int64_t bm_tasks = 0;
+    // the greedy phase starts with the task-local kernel: its workgroups (0:
+    // it is not run) and the found points each may hold
+    int32_t local_grid = 0, local_cap = 0;
     int64_t *seg_off = nullptr;   // [nq + 1] per-task segment offsets
     unsigned long long *seg_cur = nullptr;   // [nq]
     int64_t *task_out = nullptr;  // [nq] arena offset of each task's sorted list (finalization)
@@ -177,7 +181,11 @@ enum {
     CTR_LONG_TASKS = 32 * CTR_STRIDE,  // finalization: tasks a whole workgroup sorts
     CTR_SORT_QUEUE = 33 * CTR_STRIDE,  // finalization: next of them to sort
     CTR_MID_TASKS = 34 * CTR_STRIDE,   // finalization: tasks one wave sorts in LDS
-    CTR_COUNT = 35 * CTR_STRIDE
+    CTR_LOCAL_QUEUE = 35 * CTR_STRIDE, // greedy phase, task-local kernel: next task
+    CTR_LOCAL_ITEMS = 36 * CTR_STRIDE, // items it emitted or handed on
+    CTR_SPILL = 37 * CTR_STRIDE,       // of these, unexpanded ones handed to the level kernel
+    CTR_LEFT = 38 * CTR_STRIDE,        // tasks left to the level kernel from their seeds on
+    CTR_COUNT = 39 * CTR_STRIDE
 };
 
 // kernel launchers (rr_kernels.hip)

@@ -977,6 +977,8 @@ hipError_t launch_doubling(const DevIndex &ix, int64_t nq, const SearchCfg &cfg,
 hipError_t launch_beam(const DevIndex &ix, int64_t nq, const SearchCfg &cfg, SearchBufs &sb,
                        int num_cus, hipStream_t s) {
     if (nq == 0) return hipSuccess;
+    // (the beam kernel clears no bitmaps where the task-local kernel follows)
+    if (cfg.mode == RR_ADAPTIVE) plan_local(sb, ix.n, nq, num_cus);
     return dispatch_beam(ix, nq, cfg, sb, num_cus, s, SlotArgs());
 }
 
@@ -995,6 +997,7 @@ hipError_t launch_beam_slots(const DevIndex &ix, const int32_t *qlist, int64_t n
                              const SearchCfg &cfg, SearchBufs &sb, BeamState *state, void *st_d,
                              uint32_t *st_i, int32_t step_budget, int num_cus, hipStream_t s) {
     if (nwork == 0) return hipSuccess;
+    if (cfg.mode == RR_ADAPTIVE) plan_local(sb, ix.n, nwork, num_cus);
     SlotArgs sl;
     sl.qlist = qlist;
     sl.nwork = nwork;

@@ -500,39 +500,6 @@ __device__ __forceinline__ float chunk_ip_sq8(uint4 p, const uint4 *qc) {
     return a;
 }
 
-// exact distance of a float32 row for the recheck, in FP64 over the
-// zero-padded rows: the sum of squared differences, or -<x, q>
-template <bool IP>
-__device__ __forceinline__ double exact_dist_f32(const DevIndex &ix, uint32_t id,
-                                                 const uint8_t *qrow) {
-    const float4 *x = reinterpret_cast<const float4 *>(ix.base_exact + (size_t)id * ix.row_bytes_exact);
-    const float4 *q = reinterpret_cast<const float4 *>(qrow);
-    const int n4 = (ix.d + 3) / 4;
-    double a = 0.0;
-    if constexpr (IP) {
-        for (int i = 0; i < n4; ++i) {
-            const float4 u = x[i], v = q[i];
-            a = fma((double)u.x, (double)v.x, a);
-            a = fma((double)u.y, (double)v.y, a);
-            a = fma((double)u.z, (double)v.z, a);
-            a = fma((double)u.w, (double)v.w, a);
-        }
-        return -a;
-    }
-    for (int i = 0; i < n4; ++i) {
-        const float4 u = x[i], v = q[i];
-        double t = (double)u.x - (double)v.x;
-        a = fma(t, t, a);
-        t = (double)u.y - (double)v.y;
-        a = fma(t, t, a);
-        t = (double)u.z - (double)v.z;
-        a = fma(t, t, a);
-        t = (double)u.w - (double)v.w;
-        a = fma(t, t, a);
-    }
-    return a;
-}
-
 // |q|^2 part for integer data (float data needs none)
 template <int DTYPE> __device__ __forceinline__ int chunk_qq(uint4 q);
 template <> __device__ __forceinline__ int chunk_qq<RR_U8>(uint4 q) {
@@ -578,68 +545,6 @@ template <int DTYPE, int CPL, int G> struct QueryRegs {
         else qq = (int)(uint32_t)ix.key_off;
     }
 };
-
-// Evaluate the distances of candidates ci[0, k) (ids in LDS) and write them
-// to cd[0, k).  Row c is handled by lane group c % (64/G) in round c / (64/G).
-// All lanes of the wave must call this.
-template <int DTYPE, int CPL, int G, int ROUNDS_IN_FLIGHT = 8>
-__device__ __forceinline__ void eval_rows(const DevIndex &ix, const QueryRegs<DTYPE, CPL, G> &qr,
-                                          const uint32_t *ci, typename DistOf<DTYPE>::T *cd,
-                                          int k) {
-    using D = typename DistOf<DTYPE>::T;
-    using Acc = typename DistOf<DTYPE>::Acc;
-    constexpr int RPR = 64 / G;          // rows per round
-    constexpr int RB = CPL >= ROUNDS_IN_FLIGHT ? 1 : ROUNDS_IN_FLIGHT / CPL; // rounds issued together
-    const int lane = lane_id();
-    const int gl = lane & (G - 1);
-    const int grp = lane / G;
-    const int nrounds = (k + RPR - 1) / RPR;
-    for (int r0 = 0; r0 < nrounds; r0 += RB) {
-        uint4 buf[RB][CPL];
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const int c = (r0 + rb) * RPR + grp;
-            if (c < k) {
-                const uint8_t *row = ix.base + (size_t)ci[c] * (size_t)ix.row_bytes +
-                                     (size_t)gl * CPL * 16;
-#pragma unroll
-                for (int kk = 0; kk < CPL; ++kk)
-                    buf[rb][kk] = *reinterpret_cast<const uint4 *>(row + kk * 16);
-            } else {
-#pragma unroll
-                for (int kk = 0; kk < CPL; ++kk) buf[rb][kk] = make_uint4(0u, 0u, 0u, 0u);
-            }
-        }
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            Acc a = 0;
-#pragma unroll
-            for (int kk = 0; kk < CPL; ++kk) {
-                if constexpr (DTYPE == RR_BF16X)
-                    a += chunk_part_bf16(buf[rb][kk], qr.c[2 * kk], qr.c[2 * kk + 1]);
-                else if constexpr (DTYPE == RR_BF16XIP)
-                    a += chunk_ip_bf16(buf[rb][kk], qr.c[2 * kk], qr.c[2 * kk + 1]);
-                else if constexpr (DTYPE == RR_SQ8X)
-                    a += chunk_part_sq8(buf[rb][kk], &qr.c[4 * kk]);
-                else if constexpr (DTYPE == RR_SQ8XIP)
-                    a += chunk_ip_sq8(buf[rb][kk], &qr.c[4 * kk]);
-                else if constexpr (dip(DTYPE))
-                    a += chunk_ip<dbase(DTYPE)>(buf[rb][kk], qr.c[kk]);
-                else
-                    a += chunk_part<DTYPE>(buf[rb][kk], qr.c[kk]);
-            }
-            a = group_sum<G>(a);
-            const int c = (r0 + rb) * RPR + grp;
-            if (gl == 0 && c < k) {
-                if constexpr (dbase(DTYPE) == RR_SQ8X) cd[c] = a * qr.sc;
-                else if constexpr (dfloat(DTYPE)) cd[c] = dip(DTYPE) ? -a : a;
-                else if constexpr (dip(DTYPE)) cd[c] = (uint32_t)qr.qq - (uint32_t)a;
-                else cd[c] = (uint32_t)(a + qr.qq);
-            }
-        }
-    }
-    wave_sync();
-}
 
 // Evaluate up to 64 candidates ci[0, k) (ids in LDS), one per lane: returns
 // the distance of candidate `c` of this lane (meaningless where c >= k).  Row
@@ -711,6 +616,49 @@ __device__ __forceinline__ typename DistOf<DTYPE>::T eval64(const DevIndex &ix, 
     else if constexpr (dfloat(DTYPE)) return (D)(dip(DTYPE) ? -out : out);
     else if constexpr (dip(DTYPE)) return (D)((uint32_t)qr.qq - (uint32_t)out);
     else return (D)(uint32_t)(out + qr.qq);
+}
+
+// FP64 distances of up to 64 points ci[0, k) (ids in LDS) from their float32
+// rows, one per lane (meaningless from lane k on), for the approximate
+// passes' decisions.  Rows are read and summed as the float32 search reads
+// and sums them (lane groups, the same order), four rounds in flight.  One
+// lane a row, 64 different lines per load, took 37 us for a level of the
+// greedy phase on 768 values, however few points it held.
+template <bool IP>
+__device__ double exact64(const DevIndex &ix, const uint8_t *qrow, const uint32_t *ci, int k) {
+    const int chunks = ix.row_bytes_exact / 16;
+    const bool p2 = (chunks & (chunks - 1)) == 0;
+    const int g = p2 ? min(chunks, 64) : min(chunks / 3, 64), cpl = chunks / g; // row_split
+    const int lane = lane_id(), gl = lane & (g - 1), grp = lane / g, per = 64 / g;
+    const uint4 *q = reinterpret_cast<const uint4 *>(qrow) + gl * cpl;
+    double out = 0.0;
+    for (int r0 = 0; r0 * per < k; r0 += 4) {
+        const uint4 *x[4];
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t id = ci[min((r0 + r) * per + grp, k - 1)];
+            x[r] = reinterpret_cast<const uint4 *>(ix.base_exact + (uint64_t)id * (uint32_t)ix.row_bytes_exact) + gl * cpl;
+        }
+        for (int kk = 0; kk < cpl; ++kk) {
+            const uint4 y = q[kk];
+            uint4 v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = x[r][kk];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[r] += IP ? chunk_ip<RR_F32>(v[r], y) : chunk_part<RR_F32>(v[r], y);
+        }
+        for (int o = 1; o < g; o <<= 1) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[r] += __shfl_xor(s[r], o);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double v = __shfl(s[r], (lane & (per - 1)) * g);
+            out = lane / per == r0 + r ? v : out;
+        }
+    }
+    return IP ? -out : out;
 }
 
 // in-range test and early-stop tests on the exact distance
@@ -1410,6 +1358,16 @@ __global__ __launch_bounds__(512, (beam_waves<DTYPE, CPL>())) void k_beam(BeamAr
         // the sorted beam.  Approximate pass: the prefix with s <= hi holds
         // every possible member; each is re-decided on its exact distance.
         int cN = 0, cH = 0, nband = 0;
+        double dx0 = 0.0; // the first 64 candidates' exact distances
+        // exact distance of candidate base + lane
+        auto recheck = [&](int base) {
+            wave_sync();
+            ci[lane] = B.main_at(min(base + lane, nB - 1)).id();
+            wave_sync();
+            const double dx = exact64<dip(DTYPE)>(ix, qr.row, ci, min(64, cH - base));
+            wave_sync();
+            return dx;
+        };
         if constexpr (dapprox(DTYPE)) {
             for (int base = 0; base < nB; base += 64) {
                 const int i = base + lane;
@@ -1419,9 +1377,9 @@ __global__ __launch_bounds__(512, (beam_waves<DTYPE, CPL>())) void k_beam(BeamAr
             }
             for (int base = 0; base < cH; base += 64) {
                 const int i = base + lane;
-                bool inr = false;
-                if (i < cH) inr = exact_dist_f32<dip(DTYPE)>(ix, B.main_at(i).id(), qr.row) <= th.r;
-                cN += __popcll(__ballot(inr));
+                const double dx = recheck(base);
+                if (base == 0) dx0 = dx;
+                cN += __popcll(__ballot(i < cH && dx <= th.r));
                 nband += __popcll(__ballot(i < cH && B.main_at(i).dist() > th.lo));
             }
         } else {
@@ -1485,54 +1443,35 @@ __global__ __launch_bounds__(512, (beam_waves<DTYPE, CPL>())) void k_beam(BeamAr
             int64_t t = 0;
             if (lane == 0) t = (int64_t)atomicAdd(&a.sb.counters[CTR_TASKS], 1ull);
             t = uniform64(t);
-            if (expand) tset_clear(a.sb, t);
+            // (the task-local kernel clears, or writes, the bitmaps it needs)
+            if (expand && a.sb.local_grid == 0) tset_clear(a.sb, t);
             bool full = false;
-            int written = 0;
             O *idist = (O *)a.sb.item_dist;
+            int64_t off = 0;
+            if (lane == 0)
+                off = (int64_t)(atomicAdd(&a.sb.level_cnt[0], (unsigned long long)cN));
+            off = uniform64(off);
+            auto put = [&](int64_t o, uint32_t id, O d) {
+                if (o >= a.sb.item_cap) {
+                    full = true;
+                    return;
+                }
+                a.sb.item_key[o] = ((unsigned long long)(uint32_t)t << 32) | id;
+                idist[o] = d;
+            };
             if constexpr (dapprox(DTYPE)) {
+                int64_t o = off;
                 for (int base = 0; base < cH; base += 64) {
                     const int i = base + lane;
-                    double dx = 0.0;
-                    bool inr = false;
-                    if (i < cH) {
-                        dx = exact_dist_f32<dip(DTYPE)>(ix, B.main_at(i).id(), qr.row);
-                        inr = dx <= th.r;
-                    }
-                    const unsigned long long im = __ballot(inr);
-                    const int m = __popcll(im);
-                    if (m == 0) continue;
-                    int64_t off = 0;
-                    if (lane == 0)
-                        off = (int64_t)(atomicAdd(&a.sb.level_cnt[0], (unsigned long long)m));
-                    off = uniform64(off);
-                    const int64_t o = off + mbcnt(im);
-                    const bool wr = inr && o < a.sb.item_cap;
-                    if (wr) {
-                        const uint32_t id = B.main_at(i).id();
-                        a.sb.item_key[o] = ((unsigned long long)(uint32_t)t << 32) | id;
-                        idist[o] = dx;
-                    }
-                    const int mw = __popcll(__ballot(wr));
-                    written += mw;
-                    if (mw < m) full = true;
+                    const double dx = base == 0 ? dx0 : recheck(base);
+                    const unsigned long long im = __ballot(i < cH && dx <= th.r);
+                    if ((im >> lane) & 1ull) put(o + mbcnt(im), B.main_at(i).id(), dx);
+                    o += __popcll(im);
                 }
             } else {
-                int64_t off = 0;
-                if (lane == 0)
-                    off = (int64_t)(atomicAdd(&a.sb.level_cnt[0], (unsigned long long)cN));
-                off = uniform64(off);
-                for (int i = lane; i < cN; i += 64) {
-                    const int64_t o = off + i;
-                    if (o >= a.sb.item_cap) {
-                        full = true;
-                        continue;
-                    }
-                    const uint32_t id = B.main_at(i).id();
-                    a.sb.item_key[o] = ((unsigned long long)(uint32_t)t << 32) | id;
-                    idist[o] = (O)B.main_at(i).dist();
-                }
-                written = (int)max((int64_t)0, min((int64_t)cN, a.sb.item_cap - off));
+                for (int i = lane; i < cN; i += 64) put(off + i, B.main_at(i).id(), (O)B.main_at(i).dist());
             }
+            const int written = (int)max((int64_t)0, min((int64_t)cN, a.sb.item_cap - off));
             const bool lost = __ballot(full) != 0ull;
             if (lost) {
                 st.truncated = 1;
@@ -1546,6 +1485,7 @@ __global__ __launch_bounds__(512, (beam_waves<DTYPE, CPL>())) void k_beam(BeamAr
                 a.sb.task_evals[t] = 0ull;
                 a.sb.task_rechk[t] = 0ull;
                 a.sb.task_expand[t] = expand ? 1 : 0;
+                a.sb.task_seed[t] = off;
                 a.sb.res_off[q] = 0;
                 a.sb.res_cnt[q] = 0;
             }
@@ -1764,6 +1704,39 @@ __global__ __launch_bounds__(512) void k_doubling(DoublingArgs a) {
     }
 }
 
+// In-range decision of up to 64 candidates ci[0, k) (ids in LDS), one per
+// lane: `in` marks the lanes whose candidate `id`, at distance `d`, lies in
+// the ball.  Approximate passes decide exactly every candidate at or below
+// the band's upper edge (xi: 64 ids of scratch) and count those above its
+// lower one.
+template <int DTYPE, int CPL, int G>
+__device__ __forceinline__ void decide64(const DevIndex &ix, const QueryRegs<DTYPE, CPL, G> &qr, const QThresh &th,
+                                         const uint32_t *ci, int k, uint32_t *xi, typename DistOf<DTYPE>::O &d,
+                                         uint32_t &id, bool &in, unsigned long long &band) {
+    int c = 0;
+    const auto s = eval64<DTYPE, CPL, G>(ix, qr, ci, k, c);
+    id = ci[min(c, k - 1)];
+    if constexpr (dapprox(DTYPE)) {
+        const int lane = lane_id();
+        const bool need = c < k && s <= th.hi;
+        const unsigned long long m = __ballot(need);
+        in = false;
+        if (!m) return;
+        band += (unsigned long long)__popcll(__ballot(need && s > th.lo));
+        wave_sync();
+        if (need) xi[mbcnt(m)] = id;
+        wave_sync();
+        const int n = __popcll(m);
+        d = exact64<dip(DTYPE)>(ix, qr.row, xi, n);
+        id = xi[min(lane, n - 1)];
+        in = lane < n && d <= th.r;
+        wave_sync();
+    } else {
+        d = s;
+        in = c < k && in_range<typename DistOf<DTYPE>::T>(s, th);
+    }
+}
+
 // --------------------------------------------------------------------------
 // greedy phase: Algorithm 2 for all tasks at once, level-synchronous
 // --------------------------------------------------------------------------
@@ -1795,7 +1768,7 @@ template <int DTYPE, int CPL> constexpr int greedy_waves() {
 template <typename D, typename O, int GW> struct GreedyLds {
     unsigned long long cache[GREEDY_CACHE];
     uint32_t ci[GW][GREEDY_QUEUE];
-    D cd[GW][GREEDY_QUEUE];
+    uint32_t xi[GW][64]; // approximate passes: ids to decide exactly
     uint32_t st_id[GW][GREEDY_STAGE];
     int32_t st_task[GW][GREEDY_STAGE];
     O st_d[GW][GREEDY_STAGE];
@@ -2001,7 +1974,6 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
     const DevIndex &ix = a.ix;
     const int R = ix.R;
     uint32_t *qi = L.ci[wid]; // candidate queue: ids inserted into the global set
-    D *qd = L.cd[wid];        // their distances once evaluated
     const int64_t hmask = a.sb.hash_cap - 1;
     const int64_t ntasks = (int64_t)a.sb.counters[CTR_TASKS];
     uint32_t set_ops = 0; // global set updates of the wave (a wave-uniform count)
@@ -2018,34 +1990,56 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
     int lvl = 0;
     bool grouped = true;
     const int64_t regroup_min = 512 * (int64_t)gridDim.x;
-    {
-        // level 0 (the beam kernel's seeds, N of each expanding task) joins
-        // the (task, id) set before any expansion.  The beam kernel cleared
-        // the bitmaps; the kernel boundary orders those stores before these
-        // updates.
-        const int64_t c0 = min((int64_t)__hip_atomic_load(&a.sb.level_cnt[0], __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT),
-                               a.sb.item_cap);
-        bool full = false;
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c0;
-             i += (int64_t)gridDim.x * blockDim.x) {
-            const unsigned long long key = a.sb.item_key[i];
-            const int32_t t = (int32_t)(key >> 32);
-            if (t < 0 || t >= ntasks || !a.sb.task_expand[t]) continue;
-            bool f = false;
-            tset_add(a.sb, hmask, t, (uint32_t)key, f);
-            if (f) {
-                a.sb.task_trunc[t] = 1;
-                full = true;
-            }
+    // Level 0: the seeds (N of each expanding task), written by the beam
+    // kernel.  Level 1: what the task-local kernel found and expanded.  Level
+    // 2: the unexpanded points it handed on, and what the seeds of the tasks
+    // it left find here.
+    auto level_size = [&](int l) {
+        return (int64_t)__hip_atomic_load(&a.sb.level_cnt[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    const bool local = a.sb.local_grid > 0;
+    const int64_t left = local ? (int64_t)a.sb.counters[CTR_LEFT] : ntasks;
+    const int64_t spilled = local ? (int64_t)a.sb.counters[CTR_SPILL] : 0;
+    const int64_t size0 = level_size(0), size1 = local ? level_size(1) : 0;
+    if (local && left == 0 && spilled == 0) {
+        if (clock_lane) {
+            a.sb.counters[CTR_LEVELS] = size0 > 0 ? 2 : 0;
+            a.sb.counters[CTR_GREEDY_ITEMS] = (unsigned long long)(size0 + size1);
         }
+        return;
+    }
+    {
+        // the seeds join the (task, id) set before any expansion (the bitmaps
+        // were cleared by an earlier kernel: its end orders those stores
+        // before these updates); points handed on move to level 2
+        const int64_t c0 = min(size0, a.sb.item_cap), b2 = size0 + size1;
+        bool full = false;
+        const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+        if (left > 0)
+            for (int64_t i = i0; i < c0; i += stride) {
+                const unsigned long long key = a.sb.item_key[i];
+                const int32_t t = (int32_t)(key >> 32);
+                if (t < 0 || t >= ntasks || a.sb.task_expand[t] != 1) continue;
+                bool f = false;
+                tset_add(a.sb, hmask, t, (uint32_t)key, f);
+                if (f) {
+                    a.sb.task_trunc[t] = 1;
+                    full = true;
+                }
+            }
+        for (int64_t i = i0; i < spilled; i += stride)
+            if (b2 + i < a.sb.item_cap) {
+                a.sb.u_key[b2 + i] = a.sb.item_key[a.sb.item_cap - 1 - i];
+                ((O *)a.sb.u_dist)[b2 + i] = ((const O *)a.sb.item_dist)[a.sb.item_cap - 1 - i];
+            }
+        if (clock_lane && spilled > 0) atomicAdd(&a.sb.level_cnt[2], (unsigned long long)spilled);
         if (__ballot(full) && lane == 0) atomicOr(&a.sb.counters[CTR_OVERFLOW], 8ull);
         grid_sync();
     }
-    for (; lvl < a.sb.max_levels - 1; ++lvl) {
-        const int64_t cnt = (int64_t)__hip_atomic_load(&a.sb.level_cnt[lvl], __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
+    for (; lvl < a.sb.max_levels - 1;) {
+        const int64_t cnt = lvl == 0 ? size0 + size1 : level_size(lvl);
         if (cnt == 0) break;
+        const int nx = lvl == 0 && local ? 2 : lvl + 1;
         const int64_t next_base = base + cnt;
         for (int i = threadIdx.x; i < GREEDY_CACHE; i += blockDim.x) L.cache[i] = ~0ull;
         if (lane == 0) L.st_n[wid] = 0;
@@ -2054,7 +2048,9 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
         // or the unsorted level as emitted
         const unsigned long long *src_key = grouped ? a.sb.item_key : a.sb.u_key;
         // this workgroup's block of the level (items beyond item_cap were dropped)
-        const int64_t avail = max((int64_t)0, min(cnt, a.sb.item_cap - base));
+        // (level 0: the seeds, without level 1)
+        const int64_t avail = lvl == 0 ? (left > 0 ? min(size0, a.sb.item_cap) : 0)
+                                       : max((int64_t)0, min(cnt, a.sb.item_cap - base));
         const int64_t per = (avail + gridDim.x - 1) / gridDim.x;
         const int64_t i0 = min(avail, xcd_block() * per), i1 = min(avail, i0 + per);
 
@@ -2067,33 +2063,15 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
 
         // distances of the queued candidates in one gather; in-range ones are
         // staged for the next level
-        auto flush = [&]() {
+        auto flush = [&]() __attribute__((always_inline)) {
             const int k = qn;
             if (k == 0) return;
-            eval_rows<DTYPE, CPL, G>(ix, qr, qi, qd, k);
             for (int b0 = 0; b0 < k; b0 += 64) {
-                const int i = b0 + lane;
+                const int kb = min(64, k - b0);
                 bool inr = false;
                 O myd = dmax<O>();
                 uint32_t myi = 0;
-                if (i < k) {
-                    myi = qi[i];
-                    if constexpr (dapprox(DTYPE)) {
-                        // approximate distance above hi: provably outside the
-                        // ball; otherwise the exact distance decides
-                        if (qd[i] <= th.hi) {
-                            myd = exact_dist_f32<dip(DTYPE)>(ix, myi, qr.row);
-                            inr = myd <= th.r;
-                        }
-                    } else {
-                        myd = qd[i];
-                        inr = in_range<D>(qd[i], th);
-                    }
-                }
-                if constexpr (dapprox(DTYPE)) {
-                    const int nb = __popcll(__ballot(i < k && qd[i] > th.lo && qd[i] <= th.hi));
-                    run_rechk += (unsigned long long)nb;
-                }
+                decide64<DTYPE, CPL, G>(ix, qr, th, qi + b0, kb, L.xi[wid], myd, myi, inr, run_rechk);
                 const unsigned long long im = __ballot(inr);
                 const int m = __popcll(im);
                 if (m == 0) continue;
@@ -2101,7 +2079,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
                 if (sn + m > GREEDY_STAGE) {
                     // stage full: reserve for it now
                     unsigned long long o = 0;
-                    if (lane == 0) o = atomicAdd(&a.sb.level_cnt[lvl + 1], (unsigned long long)sn);
+                    if (lane == 0) o = atomicAdd(&a.sb.level_cnt[nx], (unsigned long long)sn);
                     o = __shfl(o, 0);
                     greedy_emit(L, wid, sn, next_base + (int64_t)o, a.sb);
                     wave_sync();
@@ -2119,7 +2097,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
             }
             qn = 0;
         };
-        auto close_task = [&]() {
+        auto close_task = [&]() __attribute__((always_inline)) {
             if (qtask >= 0 && lane == 0) {
                 if (run_evals) atomicAdd(&a.sb.task_evals[qtask], run_evals);
                 if (run_rechk) atomicAdd(&a.sb.task_rechk[qtask], run_rechk);
@@ -2128,7 +2106,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
             run_rechk = 0;
         };
         // queue the lanes' ids in `mask` (new members of task t's set)
-        auto enqueue = [&](int32_t t, unsigned long long mask, bool mine, int32_t f) {
+        auto enqueue = [&](int32_t t, unsigned long long mask, bool mine, int32_t f) __attribute__((always_inline)) {
             if (t != qtask) {
                 flush();
                 close_task();
@@ -2165,6 +2143,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
             tv = v ? t : -1;
             const int32_t ts = v ? t : 0, ps = v ? p : 0;
             e = a.sb.task_expand[ts];
+            if (lvl == 0) e = e == 1; // 2: the seeds were expanded by the task-local kernel
             f = ix.adj[(size_t)ps * (size_t)R + (size_t)max(0, min(lane, R - 1))];
         };
         // the set update of a pair: neighbours not yet known to the workgroup
@@ -2174,7 +2153,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
             uint32_t oA, oB;
             bool bA, bB, xA, xB;
         };
-        auto issue = [&](int32_t tA, int32_t fA, int eA, int32_t tB, int32_t fB, int eB, Pend &P) {
+        auto issue = [&](int32_t tA, int32_t fA, int eA, int32_t tB, int32_t fB, int eB, Pend &P) __attribute__((always_inline)) {
             const bool okA = tA >= 0 && eA && lane < R && fA >= 0;
             const bool okB = tB >= 0 && eB && lane < R && fB >= 0;
             const unsigned long long keyA = ((unsigned long long)(uint32_t)tA << 32) | (uint32_t)fA;
@@ -2203,7 +2182,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
                 if (__ballot(full) && lane == 0) atomicOr(&a.sb.counters[CTR_OVERFLOW], 8ull);
             }
         };
-        auto consume = [&](int32_t tA, int32_t fA, int32_t tB, int32_t fB, const Pend &P) {
+        auto consume = [&](int32_t tA, int32_t fA, int32_t tB, int32_t fB, const Pend &P) __attribute__((always_inline)) {
             const bool nA = P.bA ? !(P.oA & (1u << (fA & 31))) : P.xA;
             const bool nB = P.bB ? !(P.oB & (1u << (fB & 31))) : P.xB;
             const unsigned long long mA = __ballot(nA), mB = __ballot(nB);
@@ -2265,7 +2244,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
         if (threadIdx.x == 0) {
             unsigned long long tot = 0;
             for (int w = 0; w < GREEDY_WAVES; ++w) tot += (unsigned long long)L.st_n[w];
-            L.wg_base = tot ? atomicAdd(&a.sb.level_cnt[lvl + 1], tot) : 0ull;
+            L.wg_base = tot ? atomicAdd(&a.sb.level_cnt[nx], tot) : 0ull;
         }
         __syncthreads();
         {
@@ -2277,10 +2256,9 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
         grid_sync();
         stamp(lvl, 0);
         // regroup the next level by task
-        const int64_t ncnt = (int64_t)__hip_atomic_load(&a.sb.level_cnt[lvl + 1], __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
+        const int64_t ncnt = level_size(nx);
         if (ncnt == 0) {
-            ++lvl;
+            lvl = nx;
             break;
         }
         // levels below 512 items per workgroup are expanded as emitted (their
@@ -2298,6 +2276,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
             stamp(lvl, 2);
         }
         base = next_base;
+        lvl = nx;
     }
     // the set-operation count: one global atomic per workgroup (one per wave,
     // all arriving together at the end, would serialize on the counter)
@@ -2321,7 +2300,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
                                                          __HIP_MEMORY_SCOPE_AGENT);
             const int64_t lo = b0, hi = min(b0 + c, a.sb.item_cap);
             b0 += c;
-            const bool in_items = l == 0 || c >= regroup_min;
+            const bool in_items = l == 0 || (local && l == 1) || c >= regroup_min;
             if (limit && l == lvl)
                 for (int64_t i = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < hi;
                      i += (int64_t)gridDim.x * blockDim.x)
@@ -2343,6 +2322,285 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
         if (lvl == a.sb.max_levels - 1 &&
             __hip_atomic_load(&a.sb.level_cnt[lvl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
             atomicOr(&a.sb.counters[CTR_OVERFLOW], 16ull);
+    }
+}
+
+// --------------------------------------------------------------------------
+// greedy phase, first part: one workgroup per task
+// --------------------------------------------------------------------------
+
+// Algorithm 2 of one task inside one workgroup.  The set of evaluated points
+// is a bitmap of n bits in LDS (up to 1.1M points: 160 KB a CU), so a probe is
+// one LDS atomic; there are no levels, no grid barrier, no bitmap in memory
+// to clear.  Waves take the found points in the order of their list: wave
+// tickets run through the seeds, then through the list, and a wave whose
+// ticket is ahead of the list waits until the point is there or every point
+// taken has been finished.
+//
+// A large ball would keep one workgroup busy while the others are idle, so a
+// task is handed on when most workgroups are out of tasks and its backlog is
+// long, or when its list is full: the bitmap goes to memory (or its ids to the
+// hash table) and the unexpanded points to the level kernel, which spreads
+// them over the GPU.
+//
+// What bounds it: a wave's chain of two reads (adjacency row, base rows) per
+// point, with 8 to 16 waves a CU.  The level kernel alone spends most of its
+// time on atomics of the memory's set (13 to 16 G/s reached) and, on small
+// levels, on barriers.  Both kernels, before and now: 10,000 queries of the 1M
+// x 128 uint8 Vamana workload (642K points, lists up to 6.8K) 0.71 -> 0.53 ms;
+// 156K points, lists up to 1.4K 0.67 -> 0.26 ms; 1M x 96 bfloat16 pass, 3.6M
+// points 13.1 -> 6.0 ms; 100K x 768 8-bit pass, 45K points 1.16 -> 0.56 ms.
+// Handing on at a backlog of 384 or 1,024 points took 1 and 4% longer on the
+// first, at an idle half or quarter of the workgroups 5 and 9%.
+constexpr int LOCAL_SEEDS = 32;      // tasks with more seeds start in the level kernel
+constexpr int LOCAL_LIST = 8192;     // found points a workgroup can hold at most
+constexpr int LOCAL_IDLE = 6;        // eighths of the workgroups out of tasks, and
+constexpr int LOCAL_BACKLOG = 192;   // points waiting, from which the level kernel is worth its start
+// the list is stopped this far from its end: every wave may still add the
+// neighbours of the point it is at, and so may every seed not yet taken
+constexpr int local_margin(int waves, int seeds) { return (waves + seeds) * 64; }
+
+// Whether the task-local kernel runs, with how many workgroups and how long a
+// list each (a list's distances lie in the finalization's item_cap entries,
+// which are free until then).  It needs the bitmap and the list in LDS, a
+// list some way above the margin, and a workgroup for every CU or query.
+inline void plan_local(SearchBufs &sb, int64_t n, int64_t nq, int num_cus) {
+    sb.local_grid = sb.local_cap = 0;
+    const int64_t words = bitmap_words(n), least = local_margin(16, LOCAL_SEEDS) + 256;
+    const int64_t lds = 160 * 1024, fix = words * 4 + 16 * 64 * 8 + 512;
+    if (nq <= 0 || fix + least * 4 > lds) return;
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(4, lds / (fix + LOCAL_LIST * 4)));
+    const int64_t grid = std::min(std::min(nq, per_cu * num_cus), sb.item_cap / least);
+    if (grid < std::min<int64_t>(nq, num_cus)) return;
+    const int64_t list = std::min<int64_t>(LOCAL_LIST, (lds / per_cu - fix) / 4);
+    sb.bm_words = words;
+    sb.local_grid = (int32_t)grid;
+    sb.local_cap = (int32_t)(std::min<int64_t>(list, sb.item_cap / grid) & ~3ll);
+}
+
+struct LocalTask {
+    int head, tail, done, stop; // tickets given, points found, points finished
+    int task, ns, nd, cs, cd;
+    unsigned evals, rechk;
+    unsigned long long base_d, base_s;
+    long long keep_d, keep_s;
+};
+inline size_t local_lds(int64_t bm_words, int cap, int gw, bool approx) {
+    return (size_t)bm_words * 4 + (size_t)cap * 4 + (size_t)gw * 64 * (approx ? 8 : 4) + sizeof(LocalTask);
+}
+
+// waves per workgroup: as many as the registers of the distance code leave
+template <int DTYPE, int CPL> constexpr int local_waves() {
+    return dfloat(DTYPE) ? (dbase(DTYPE) == RR_SQ8X && CPL >= 3 ? 8 : 12) : CPL >= 6 ? 12 : 16;
+}
+
+template <int DTYPE, int CPL, int G>
+__global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_local(GreedyArgs a) {
+    using O = typename DistOf<DTYPE>::O;
+    constexpr int GW = local_waves<DTYPE, CPL>();
+    extern __shared__ __align__(16) uint8_t local_smem[];
+    uint32_t *const bm = reinterpret_cast<uint32_t *>(local_smem);
+    const int64_t words = a.sb.bm_words;
+    const int cap = a.sb.local_cap;
+    volatile uint32_t *const ids = bm + words;
+    const int lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t *const ci = bm + words + cap + wid * 64;
+    uint32_t *const xi = bm + words + cap + (GW + wid) * 64; // approximate passes
+    LocalTask &T = *reinterpret_cast<LocalTask *>(bm + words + cap + (dapprox(DTYPE) ? 2 : 1) * GW * 64);
+    volatile int *const v_head = &T.head, *const v_tail = &T.tail, *const v_done = &T.done, *const v_stop = &T.stop;
+    const DevIndex &ix = a.ix;
+    const int R = ix.R;
+    const int64_t ntasks = (int64_t)a.sb.counters[CTR_TASKS];
+    const int64_t size0 = min((int64_t)a.sb.level_cnt[0], a.sb.item_cap);
+    O *const idist = (O *)a.sb.item_dist;
+    O *const sc = (O *)a.sb.seg_dists + (int64_t)blockIdx.x * cap; // the list's distances
+    unsigned long long *const queue = &a.sb.counters[CTR_LOCAL_QUEUE];
+    const int64_t idle = (int64_t)gridDim.x * LOCAL_IDLE / 8;
+
+    for (;;) {
+        if (threadIdx.x == 0) {
+            T.task = (int)atomicAdd(queue, 1ull);
+            T.head = T.tail = T.done = T.stop = 0;
+            T.evals = T.rechk = 0u;
+            T.ns = T.nd = T.cs = T.cd = 0;
+        }
+        __syncthreads();
+        const int t = __builtin_amdgcn_readfirstlane(T.task);
+        if (t >= ntasks) break;
+        const int nseed = (int)a.sb.task_cnt[t];
+        if (!a.sb.task_expand[t] || nseed > LOCAL_SEEDS) {
+            if (a.sb.task_expand[t]) {
+                // left to the level kernel, which starts from an empty set
+                if (t < a.sb.bm_tasks)
+                    for (int64_t i = threadIdx.x; i < words / 4; i += blockDim.x)
+                        reinterpret_cast<uint4 *>(a.sb.bm + t * words)[i] = make_uint4(0u, 0u, 0u, 0u);
+                if (threadIdx.x == 0) atomicAdd(&a.sb.counters[CTR_LEFT], 1ull);
+            }
+            __syncthreads(); // T is written again
+            continue;
+        }
+        const int64_t seed0 = a.sb.task_seed[t];
+        const int32_t q = __builtin_amdgcn_readfirstlane(a.sb.task_q[t]);
+        for (int64_t i = threadIdx.x; i < words / 4; i += blockDim.x)
+            reinterpret_cast<uint4 *>(bm)[i] = make_uint4(0u, 0u, 0u, 0u);
+        for (int i = threadIdx.x; i < cap; i += blockDim.x) ids[i] = RR_EMPTY32;
+        const QThresh th = a.sb.qth[q];
+        QueryRegs<DTYPE, CPL, G> qr;
+        qr.load(a.sb.qpad + (size_t)q * qrow_stride<DTYPE>(ix), ix);
+        __syncthreads();
+        if (threadIdx.x < nseed) {
+            const uint32_t id = (uint32_t)a.sb.item_key[seed0 + threadIdx.x];
+            atomicOr(&bm[id >> 5], 1u << (id & 31));
+        }
+        __syncthreads();
+        unsigned evals = 0;
+        unsigned long long rechk = 0;
+        // a wave takes its next ticket, and loads its adjacency row if the
+        // point is there already, before it evaluates the current neighbours
+        auto ticket = [&]() {
+            int i = 0;
+            if (lane == 0) i = atomicAdd(&T.head, 1);
+            return (int)__builtin_amdgcn_readfirstlane(i);
+        };
+        auto row = [&](uint32_t p) { return ix.adj[(uint64_t)p * (uint32_t)R + max(0, min(lane, R - 1))]; };
+        int i = ticket();
+        uint32_t np = RR_EMPTY32; // the ticket's point, if it is known
+        int32_t nf = -1;          // and its row
+        for (;;) {
+            uint32_t p = np;
+            const int k0 = i - nseed;
+            if (k0 < 0) {
+                if (p == RR_EMPTY32) p = (uint32_t)a.sb.item_key[seed0 + i];
+            } else {
+                uint32_t v = RR_EMPTY32;
+                for (;;) {
+                    if (*v_stop) break;
+                    if (k0 < cap) v = ids[k0];
+                    if (v != RR_EMPTY32) break;
+                    // every point found is finished: no more will come (`done`
+                    // is read before `tail`, and a wave adds to `tail` before
+                    // it adds to `done`)
+                    const int d = *v_done;
+                    if (d == nseed + *v_tail) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                p = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+                if (p == RR_EMPTY32) break;
+                // now and then: how many workgroups are out of tasks?  (each of
+                // them has taken one ticket past the end)
+                if ((k0 & 31) == 0 && *v_tail - k0 > LOCAL_BACKLOG &&
+                    (int64_t)__hip_atomic_load(queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= ntasks + idle) {
+                    if (lane == 0) *v_stop = 1;
+                }
+            }
+            const int32_t f = np == p ? nf : row(p);
+            bool cand = false;
+            if (lane < R && f >= 0) {
+                const uint32_t bit = 1u << (f & 31);
+                cand = !(atomicOr(&bm[(uint32_t)f >> 5], bit) & bit);
+            }
+            const unsigned long long cm = __ballot(cand);
+            const int k = __popcll(cm);
+            evals += (unsigned)k;
+            const int ni = ticket();
+            np = RR_EMPTY32;
+            if (ni < nseed) np = (uint32_t)a.sb.item_key[seed0 + ni];
+            else if (ni - nseed < cap) np = (uint32_t)__builtin_amdgcn_readfirstlane((int)ids[ni - nseed]);
+            if (np != RR_EMPTY32) nf = row(np);
+            if (k > 0) {
+                if (cand) ci[mbcnt(cm)] = (uint32_t)f;
+                wave_sync();
+                bool in = false;
+                O d = dmax<O>();
+                uint32_t id = 0;
+                decide64<DTYPE, CPL, G>(ix, qr, th, ci, k, xi, d, id, in, rechk);
+                wave_sync();
+                const unsigned long long im = __ballot(in);
+                if (im) {
+                    const int m = __popcll(im);
+                    int pos = 0;
+                    if (lane == 0) pos = atomicAdd(&T.tail, m);
+                    pos = __builtin_amdgcn_readfirstlane(pos);
+                    // (this wave's points are in; a seed taken after `head` is
+                    // read is counted all the same)
+                    if (pos + m > cap - local_margin(GW, max(0, nseed - *v_head)) && lane == 0) *v_stop = 1;
+                    const int o = pos + mbcnt(im);
+                    if (in) {
+                        sc[o] = d;
+                        ids[o] = id; // (o < cap: the margin)
+                    }
+                }
+            }
+            wave_sync();
+            if (lane == 0) {
+                if (i >= nseed) ids[i - nseed] = p | 0x80000000u; // expanded
+                atomicAdd(&T.done, 1);
+            }
+            i = ni;
+        }
+        if (lane == 0) {
+            atomicAdd(&T.evals, evals);
+            if (rechk) atomicAdd(&T.rechk, (unsigned)rechk);
+        }
+        __syncthreads();
+        // the list: expanded points become items of level 1, the others are
+        // handed on from the top of the item arrays
+        const int n = T.tail;
+        const bool stopped = T.stop != 0;
+        if (stopped) {
+            int u = 0;
+            for (int i = threadIdx.x; i < n; i += blockDim.x) u += ids[i] & 0x80000000u ? 0 : 1;
+            if (u) atomicAdd(&T.ns, u);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const long long ns = T.ns, nd = n - ns;
+            // both parts fit between the seeds and the end of the arrays, or
+            // the rest is dropped
+            const long long old = n ? (long long)atomicAdd(&a.sb.counters[CTR_LOCAL_ITEMS], (unsigned long long)n) : 0;
+            const long long room = max(0ll, (long long)(a.sb.item_cap - size0) - old);
+            T.keep_d = min(nd, room);
+            T.keep_s = min(ns, room - T.keep_d);
+            T.base_d = T.keep_d ? atomicAdd(&a.sb.level_cnt[1], (unsigned long long)T.keep_d) : 0ull;
+            T.base_s = T.keep_s ? atomicAdd(&a.sb.counters[CTR_SPILL], (unsigned long long)T.keep_s) : 0ull;
+            if (T.keep_d + T.keep_s < n) {
+                a.sb.task_trunc[t] = 1;
+                atomicOr(&a.sb.counters[CTR_OVERFLOW], 4ull);
+            }
+            a.sb.task_cnt[t] = (unsigned long long)(nseed + T.keep_d + T.keep_s);
+            a.sb.task_prev[t] = (unsigned long long)(nseed + T.keep_d);
+            a.sb.task_evals[t] = T.evals;
+            a.sb.task_rechk[t] = T.rechk;
+            a.sb.task_expand[t] = 2;
+        }
+        __syncthreads();
+        const unsigned long long tk = (unsigned long long)(uint32_t)t << 32;
+        for (int i = threadIdx.x; i < n; i += blockDim.x) {
+            const uint32_t v = ids[i];
+            const bool on = stopped && !(v & 0x80000000u);
+            const int j = !stopped ? i : atomicAdd(on ? &T.cs : &T.cd, 1);
+            if (j >= (on ? T.keep_s : T.keep_d)) continue;
+            const int64_t o = on ? a.sb.item_cap - 1 - (int64_t)T.base_s - j : size0 + (int64_t)T.base_d + j;
+            a.sb.item_key[o] = tk | (v & 0x7fffffffu);
+            idist[o] = sc[i];
+        }
+        if (T.keep_s > 0) {
+            if (t < a.sb.bm_tasks) {
+                for (int64_t i = threadIdx.x; i < words / 4; i += blockDim.x)
+                    reinterpret_cast<uint4 *>(a.sb.bm + t * words)[i] = reinterpret_cast<const uint4 *>(bm)[i];
+            } else {
+                bool full = false;
+                for (int64_t i = threadIdx.x; i < words; i += blockDim.x)
+                    for (uint32_t w = bm[i]; w; w &= w - 1)
+                        gset_insert(a.sb.hash, a.sb.hash_cap - 1, tk | (uint32_t)(32 * i + __ffs((int)w) - 1), full);
+                if (full) {
+                    a.sb.task_trunc[t] = 1;
+                    atomicOr(&a.sb.counters[CTR_OVERFLOW], 8ull);
+                }
+            }
+        }
+        __syncthreads(); // T and the list are written again
     }
 }
 
@@ -2412,6 +2670,19 @@ static hipError_t run_greedy(const DevIndex &ix, const SearchCfg &cfg, SearchBuf
     if (e != hipSuccess) return e;
     if (per_cu < 1) return hipErrorInvalidConfiguration;
     if (per_cu > 2) per_cu = 2;
+    if (sb.local_grid > 0) {
+        auto lk = k_greedy_local<DTYPE, CPL, G>;
+        constexpr int LW = local_waves<DTYPE, CPL>();
+        const size_t lsm = local_lds(sb.bm_words, sb.local_cap, LW, dapprox(DTYPE));
+        int n = 0;
+        e = kernel_occupancy((const void *)lk, LW * 64, lsm, &n);
+        if (e != hipSuccess) return e;
+        if (n < 1) return hipErrorInvalidConfiguration;
+        const int lg = (int)std::min<int64_t>(sb.local_grid, (int64_t)n * num_cus);
+        hipLaunchKernelGGL(lk, dim3(lg), dim3(LW * 64), lsm, s, a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     // the level barriers need every workgroup resident: a cooperative launch
     dim3 grid((unsigned)(per_cu * num_cus)), block(GW * 64);
     void *args[] = {&a};
