@@ -17,6 +17,7 @@ struct ScanArgs {
     const QThresh *qth;   // [nq] (range mode)
     int64_t nq;
     int64_t chunk;        // base points per workgroup
+    int32_t qblocks;      // query blocks (integer range scan)
     // nn mode
     unsigned long long *nn_bits; // [nq] min distance bits (uint32 value or double bits)
     // range mode: hits appended as items (task = query)

@@ -3,7 +3,8 @@
 // Definition 2.1 evaluated for every pair: K_q = { p : d(p, q) <= r_q }, plus
 // the per-query nearest-neighbour distance used to choose radii.  The scan is
 // a dense contraction Q X^T, so it runs on MFMA:
-//  * uint8 / int8: v_mfma_i32_16x16x64_i8.  uint8 values are shifted by -128
+//  * uint8 / int8: v_mfma_i32_16x16x64_i8 (nearest distances) and
+//    v_mfma_i32_32x32x32_i8 (range).  uint8 values are shifted by -128
 //    (x ^ 0x80) into int8; squared distances are shift invariant, so
 //    d = |q'|^2 + |x'|^2 - 2 q'.x' is exact in int32.
 //  * float32: a bfloat16 filter with an exact FP64 decision
@@ -85,11 +86,9 @@ __device__ __forceinline__ int row_sum_u8(uint4 v, int s) {
     return (int)t;
 }
 
-// MODE (SCAN_NN / SCAN_RANGE) is a template parameter so that each
-// instantiation keeps only its own per-query state in registers
-template <int DTYPE, int KS, bool IP, int MODE, int QT>
+// nearest distance of every query, integer rows
+template <int DTYPE, int KS, bool IP, int QT>
 __global__ __launch_bounds__(256) void k_scan_int(ScanArgs a) {
-    constexpr int mode = MODE;
     const int lane = threadIdx.x & 63;
     const int wid = threadIdx.x >> 6;
     const int row = lane & 15, grp = lane >> 4;
@@ -98,10 +97,6 @@ __global__ __launch_bounds__(256) void k_scan_int(ScanArgs a) {
     const int64_t p_begin = (int64_t)blockIdx.y * a.chunk;
     const int64_t p_end = min(a.ix.n, p_begin + a.chunk);
     if (q0 >= a.nq || p_begin >= p_end) return;
-    __shared__ uint32_t stage[MODE == SCAN_RANGE ? 4 * 3 * SCAP : 1];
-    uint32_t *st_task = stage + wid * 3 * SCAP, *st_id = st_task + SCAP, *st_dist = st_id + SCAP;
-    int scnt = 0; // staged hits of this wave (wave-uniform)
-
     constexpr int KSMAX = KS;
     v4i A[QT][KSMAX];
     int qn_own[QT];
@@ -142,28 +137,13 @@ __global__ __launch_bounds__(256) void k_scan_int(ScanArgs a) {
     }
     // Every distance (or key) is qn + part with the query's constant qn and
     // part = |x'|^2 - 2 q'.x' (inner product: the base row's part - q.x),
-    // exact in int32.  The loop works on neg = -part = 2 q'.x' - |x'|^2 (one
-    // shift-add per element): the nearest-neighbour minimum of part is the
-    // negated maximum of neg, and the range test part <= r_int - qn is
-    // neg >= qn - r_int (saturated to int32; rows past nq never hit).  This
-    // keeps one register per (tile, row).
-    int lim[QT][4]; // SCAN_NN: the largest neg so far; SCAN_RANGE: qn - r_int
+    // exact in int32.  The loop keeps the largest neg = -part = 2 q'.x' -
+    // |x'|^2 (one shift-add and one maximum per element).
+    int lim[QT][4]; // the largest neg so far
 #pragma unroll
     for (int t = 0; t < QT; ++t)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            if (mode == SCAN_NN) {
-                lim[t][v] = INT_MIN;
-            } else {
-                // |neg| < 2^26 for every valid pair (d <= 512), so clamping
-                // the bound below at -2^28 changes no decision; rows past nq
-                // get INT_MAX, which no neg reaches
-                const int64_t q = q0 + t * 16 + 4 * grp + v;
-                const int64_t qn = __shfl(qn_own[t], 4 * grp + v);
-                lim[t][v] = q < a.nq ? (int)max(-(int64_t)(1 << 28), min((int64_t)INT_MAX, qn - a.qth[q].r_int))
-                                     : INT_MAX;
-            }
-        }
+        for (int v = 0; v < 4; ++v) lim[t][v] = INT_MIN;
 
     // the next tile's rows are loaded while the current one is multiplied
     // (clamped to the chunk's last row, so every load is in bounds)
@@ -208,9 +188,6 @@ __global__ __launch_bounds__(256) void k_scan_int(ScanArgs a) {
         xs += xor32(xs);
         if (IP) xs = -128 * xs; // the base row's part of the uint8 key (0 for int8)
         int nxs = -xs;
-        // rows past the chunk (clamped copies of its last row) get a neg
-        // below -2^28, under every range bound
-        if (mode == SCAN_RANGE && p0 + row >= p_end) nxs = -(1 << 30);
         // opaque to the optimiser, so that 2 acc + nxs stays one shift-add
         // instead of being refolded into a shift and a subtraction
         asm volatile("" : "+v"(nxs));
@@ -220,44 +197,13 @@ __global__ __launch_bounds__(256) void k_scan_int(ScanArgs a) {
 #pragma unroll
             for (int ks = 0; ks < KSMAX; ++ks)
                 if (ks < ks_n) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[t][ks], B[ks], acc, 0, 0, 0);
-            int neg[4];
-            bool any = false;
+            // rows past the chunk repeat its last row, which leaves the
+            // maximum unchanged, so no validity test is needed
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                neg[v] = IP ? acc[v] + nxs : 2 * acc[v] + nxs;
-                // SCAN_NN: rows past the chunk repeat its last row, which
-                // leaves the maximum unchanged, so no validity test is needed
-                if (mode == SCAN_NN) lim[t][v] = max(lim[t][v], neg[v]);
-                else any |= neg[v] >= lim[t][v];
-            }
-            // hits are rare: one wave-wide test per tile before the per-row work
-            if (mode == SCAN_RANGE && __ballot(any)) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const bool hit = neg[v] >= lim[t][v];
-                    const unsigned long long hm = __ballot(hit);
-                    if (hm) {
-                        const int nh = __popcll(hm);
-                        if (scnt + nh > SCAP) {
-                            flush_hits(a, st_task, st_id, st_dist, scnt, lane);
-                            scnt = 0;
-                        }
-                        const uint32_t qn = (uint32_t)__shfl(qn_own[t], 4 * grp + v);
-                        if (hit) {
-                            const int slot = scnt + (int)__builtin_amdgcn_mbcnt_hi(
-                                (unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
-                            st_task[slot] = (uint32_t)(q0 + t * 16 + 4 * grp + v);
-                            st_id[slot] = (uint32_t)(p0 + row);
-                            st_dist[slot] = qn - (uint32_t)neg[v];
-                        }
-                        scnt += nh;
-                    }
-                }
-            }
+            for (int v = 0; v < 4; ++v) lim[t][v] = max(lim[t][v], IP ? acc[v] + nxs : 2 * acc[v] + nxs);
         }
     }
-    if (mode == SCAN_RANGE && scnt > 0) flush_hits(a, st_task, st_id, st_dist, scnt, lane);
-    if (mode == SCAN_NN) {
+    {
 #pragma unroll
         for (int t = 0; t < QT; ++t)
 #pragma unroll
@@ -272,6 +218,202 @@ __global__ __launch_bounds__(256) void k_scan_int(ScanArgs a) {
                     atomicMin(&a.nn_bits[q], (unsigned long long)(qn - (uint32_t)b));
             }
     }
+}
+
+// Range scan of integer rows, v_mfma_i32_32x32x32_i8.  The four waves of a
+// workgroup stream 16 KB of base rows at a time through LDS (loaded one step
+// ahead; 16-byte chunks at a place xored by the row, so the lanes that read a
+// chunk column fall on different banks) and each multiplies them with QT tiles
+// of 32 queries that it holds in registers.
+// With lim = |q'|^2 - r a pair is a hit iff 2 q'.x' - |x'|^2 >= lim, and only
+// if q'.x' - floor(|x'|^2 / 2) >= floor(lim / 2): a lane's column is one
+// query, the sums start at the rows' half of the test (16 registers, shared by
+// the query tiles; the loading threads put it in LDS beside the rows), and
+// 16 outputs take one maximum and one compare.  A tile with a hit is
+// multiplied again and decided by the first test, so nothing but the maximum
+// has to outlive its tile.  Inner product: the same without the halving.
+// Bound by the matrix cores: 10,000 queries x 1M x 128 (2.56 T operations) are
+// 0.5 ms at the 5 POP/s dense peak, about 1.0 ms at the share of its peak that
+// a large bf16 product reaches.  16x16 tiles, with a shift-add, a compare
+// and an or for every output, took 1.74 ms; query bounds in the sums' start
+// (64 registers) and rows loaded by each wave for itself 1.50 ms, with
+// two query tiles a wave 2.47 ms; this one 1.32 ms, of which the 160,000
+// hits are 0.15 ms.
+// Output tile: lane l, register v holds row 8 (v / 4) + 4 (l / 32) + v % 4,
+// query l % 32.
+typedef int v16i __attribute__((ext_vector_type(16)));
+constexpr int range_qt(int ks) { return ks <= 6 ? 4 : ks <= 12 ? 2 : 1; }
+constexpr int range_tile(int ks) { return ks <= 4 ? 128 : ks <= 8 ? 64 : 32; } // base points per step
+constexpr int range_waves(int ks) { return ks <= 2 ? 3 : 2; }                  // per SIMD, as registers allow
+
+template <int DTYPE, int KS, bool IP, int QT>
+__global__ __launch_bounds__(256, range_waves(KS)) void k_scan_range(ScanArgs a) {
+    constexpr int CPR = 2 * KS;                   // 16-byte chunks per row
+    constexpr int TPR = CPR % 8 == 0 ? 8 : 4;     // threads that load a row together
+    constexpr int TILE = range_tile(KS), PASS = 256 / TPR;
+    constexpr int ROWS = TILE / PASS, COLS = CPR / TPR; // rows and chunks of a thread per step
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int l32 = lane & 31, half = lane >> 5;
+    // the query blocks of one chunk of the base follow each other on one XCD
+    // (workgroups are dealt to the 8 XCDs in turn), so its L2 serves them
+    const int64_t lin = blockIdx.x;
+    // up to QT * 32 queries: every wave takes them all and a fourth of the points
+    const bool few = a.nq <= QT * 32;
+    const int64_t q0 = few ? 0 : (((lin / 8) % a.qblocks) * 4 + wid) * (QT * 32);
+    const int sub0 = few ? wid * 32 : 0, sub_step = few ? 128 : 32;
+    const int64_t p_begin = (lin % 8 + 8 * ((lin / 8) / a.qblocks)) * a.chunk;
+    const int64_t p_end = min(a.ix.n, p_begin + a.chunk);
+    if (p_begin >= p_end) return;
+    const bool active = q0 < a.nq; // waves without queries only help to load
+    __shared__ uint4 xt[2][TILE * CPR];
+    __shared__ int xstart[2][TILE], xsum[2][TILE];
+    auto place = [](int row, int c) {
+        return row * CPR + (c ^ (CPR % 16 == 0 ? row & 15 : CPR % 8 == 0 ? (row >> 1) & 7 : (row >> 2) & 3));
+    };
+    __shared__ uint32_t stage[4 * 3 * SCAP];
+    uint32_t *st_task = stage + wid * 3 * SCAP, *st_id = st_task + SCAP, *st_dist = st_id + SCAP;
+    int scnt = 0; // staged hits of this wave (wave-uniform)
+    // row sums: squares of the shifted values, or for the uint8 inner product
+    // the plain values
+    auto part = [](uint4 v, uint4 w, int s) {
+        if (IP) return DTYPE == RR_U8 ? row_sum_u8(v, s) : 0;
+        s = __builtin_amdgcn_sdot4((int)w.x, (int)w.x, s, false);
+        s = __builtin_amdgcn_sdot4((int)w.y, (int)w.y, s, false);
+        s = __builtin_amdgcn_sdot4((int)w.z, (int)w.z, s, false);
+        return __builtin_amdgcn_sdot4((int)w.w, (int)w.w, s, false);
+    };
+    auto shifted = [](uint4 v) {
+        return DTYPE == RR_U8 ? make_uint4(shift_u8(v.x), shift_u8(v.y), shift_u8(v.z), shift_u8(v.w)) : v;
+    };
+    v4i Q[QT][KS];
+    int qn[QT], lim[QT]; // of the lane's query: its part of the distance, its bound
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+        const int64_t q = q0 + t * 32 + l32, qc = min(q, a.nq - 1);
+        int s = 0;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(a.qpad + qc * a.ix.row_bytes + ks * 32 + half * 16);
+            const uint4 w = shifted(v);
+            s = part(v, w, s);
+            Q[t][ks] = v4i{(int)w.x, (int)w.y, (int)w.z, (int)w.w};
+        }
+        s += xor32(s);
+        if (IP)
+            s = (int)((uint32_t)a.ix.key_off +
+                      (DTYPE == RR_U8 ? (uint32_t)(16384 * KS * 32) - 128u * (uint32_t)s : 0u));
+        qn[t] = s;
+        // every sum below is under 2^26 in magnitude (d <= 512): bounds clamped
+        // at -2^28 and 2^30 decide the same; queries past nq get 2^30
+        lim[t] = q < a.nq ? (int)max(-(int64_t)(1 << 28), min((int64_t)(1 << 30), (int64_t)s - a.qth[qc].r_int))
+                          : 1 << 30;
+    }
+    uint4 nxt[ROWS][COLS];
+    const int lrow = tid / TPR, lcol = tid % TPR;
+    auto load = [&](int64_t p0) {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+            for (int j = 0; j < COLS; ++j)
+                nxt[i][j] = *reinterpret_cast<const uint4 *>(
+                    a.ix.base + min(p0 + i * PASS + lrow, p_end - 1) * a.ix.row_bytes + (lcol + j * TPR) * 16);
+    };
+    load(p_begin);
+    int buf = 0;
+    for (int64_t s0 = p_begin; s0 < p_end; s0 += TILE, buf ^= 1) {
+        // (a wave that has passed this barrier is done with the step before, so
+        // the next step may write the other buffer)
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            const int row = i * PASS + lrow;
+            int s = 0;
+#pragma unroll
+            for (int j = 0; j < COLS; ++j) {
+                const uint4 w = shifted(nxt[i][j]);
+                s = part(nxt[i][j], w, s);
+                xt[buf][place(row, lcol + j * TPR)] = w;
+            }
+            s += __builtin_amdgcn_update_dpp(0, s, 0xB1, 0xf, 0xf, true); // lane ^ 1
+            s += __builtin_amdgcn_update_dpp(0, s, 0x4E, 0xf, 0xf, true); // lane ^ 2
+            if (TPR == 8) s += __builtin_amdgcn_update_dpp(0, s, 0x141, 0xf, 0xf, true); // the other four of eight
+            if (lcol == 0) {
+                // rows past the chunk (copies of its last row) never pass
+                xstart[buf][row] = s0 + row < p_end ? (IP ? 128 * s : -(s >> 1)) : -(1 << 29);
+                xsum[buf][row] = s;
+            }
+        }
+        __syncthreads();
+        if (s0 + TILE < p_end) load(s0 + TILE);
+        if (!active) continue;
+        for (int sub = sub0; sub < TILE && s0 + sub < p_end; sub += sub_step) {
+            v4i X[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const uint4 w = xt[buf][place(sub + l32, 2 * ks + half)];
+                X[ks] = v4i{(int)w.x, (int)w.y, (int)w.z, (int)w.w};
+            }
+            // the lane's 16 rows of the output tile
+            auto rows16 = [&](const int *of) {
+                v16i r;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int4 w = *reinterpret_cast<const int4 *>(of + sub + 8 * g + 4 * half);
+                    r[4 * g] = w.x, r[4 * g + 1] = w.y, r[4 * g + 2] = w.z, r[4 * g + 3] = w.w;
+                }
+                return r;
+            };
+            const v16i start = rows16(xstart[buf]);
+            auto sums = [&](int t) {
+                v16i acc = start;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(X[ks], Q[t][ks], acc, 0, 0, 0);
+                return acc;
+            };
+            unsigned long long some[QT], any = 0ull;
+#pragma unroll
+            for (int t = 0; t < QT; ++t) {
+                const v16i acc = sums(t);
+                int top = acc[0];
+#pragma unroll
+                for (int v = 1; v < 16; ++v) top = max(top, acc[v]);
+                some[t] = __ballot(top >= (IP ? lim[t] : lim[t] >> 1));
+                any |= some[t];
+            }
+            if (!any) continue;
+#pragma unroll
+            for (int t = 0; t < QT; ++t) {
+                if (!some[t]) continue;
+                const v16i acc = sums(t), xs = rows16(xsum[buf]);
+                int h4 = sub + 4 * half;
+                asm volatile("" : "+v"(h4)); // (sixteen sums with it would be kept through the loop)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = h4 + 8 * (v / 4) + v % 4;
+                    // q'.x' and the row's part, or 2 q'.x' - |x'|^2
+                    const int val = IP ? acc[v] : 2 * acc[v] - (xs[v] & 1);
+                    const bool hit = val >= lim[t];
+                    const unsigned long long hm = __ballot(hit);
+                    if (hm) {
+                        const int nh = __popcll(hm);
+                        if (scnt + nh > SCAP) {
+                            flush_hits(a, st_task, st_id, st_dist, scnt, lane);
+                            scnt = 0;
+                        }
+                        if (hit) {
+                            const int slot = scnt + (int)__builtin_amdgcn_mbcnt_hi(
+                                (unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
+                            st_task[slot] = (uint32_t)(q0 + t * 32 + l32);
+                            st_id[slot] = (uint32_t)(s0 + row);
+                            st_dist[slot] = (uint32_t)qn[t] - (uint32_t)val;
+                        }
+                        scnt += nh;
+                    }
+                }
+            }
+        }
+    }
+    if (scnt > 0) flush_hits(a, st_task, st_id, st_dist, scnt, lane);
 }
 
 // float32 data: FP64 MFMA (16x16x4).  A: lane l holds q[i=l%16][k=4s+l/16];
@@ -398,28 +540,42 @@ __global__ void k_identity_tasks(int32_t *task_q, int64_t nq, unsigned long long
     if (blockIdx.x == 0 && threadIdx.x == 0) counters[CTR_TASKS] = (unsigned long long)nq;
 }
 
-template <int K, int MODE>
+template <int K>
 static void launch_scan_int(const ScanArgs &a, bool ip, dim3 grid, dim3 block, hipStream_t s) {
-    if (a.ix.dtype == RR_U8 && ip) hipLaunchKernelGGL((k_scan_int<RR_U8, K, true, MODE, scan_qt(K)>), grid, block, 0, s, a);
-    else if (a.ix.dtype == RR_U8) hipLaunchKernelGGL((k_scan_int<RR_U8, K, false, MODE, scan_qt(K)>), grid, block, 0, s, a);
-    else if (ip) hipLaunchKernelGGL((k_scan_int<RR_I8, K, true, MODE, scan_qt(K)>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_scan_int<RR_I8, K, false, MODE, scan_qt(K)>), grid, block, 0, s, a);
+    if (a.ix.dtype == RR_U8 && ip) hipLaunchKernelGGL((k_scan_int<RR_U8, K, true, scan_qt(K)>), grid, block, 0, s, a);
+    else if (a.ix.dtype == RR_U8) hipLaunchKernelGGL((k_scan_int<RR_U8, K, false, scan_qt(K)>), grid, block, 0, s, a);
+    else if (ip) hipLaunchKernelGGL((k_scan_int<RR_I8, K, true, scan_qt(K)>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_scan_int<RR_I8, K, false, scan_qt(K)>), grid, block, 0, s, a);
+}
+
+template <int K>
+static void launch_scan_range(const ScanArgs &a, bool ip, dim3 grid, dim3 block, hipStream_t s) {
+    constexpr int QT = range_qt(K);
+    if (a.ix.dtype == RR_U8 && ip) hipLaunchKernelGGL((k_scan_range<RR_U8, K, true, QT>), grid, block, 0, s, a);
+    else if (a.ix.dtype == RR_U8) hipLaunchKernelGGL((k_scan_range<RR_U8, K, false, QT>), grid, block, 0, s, a);
+    else if (ip) hipLaunchKernelGGL((k_scan_range<RR_I8, K, true, QT>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_scan_range<RR_I8, K, false, QT>), grid, block, 0, s, a);
 }
 
 static hipError_t launch_scan(const ScanArgs &a0, int mode, hipStream_t s) {
     ScanArgs a = a0;
-    const int qper = a.ix.dtype == RR_F32 ? 4 * 2 * 16 : 4 * scan_qt(a.ix.row_bytes / 64) * 16;
+    const int qper = a.ix.dtype == RR_F32 ? 4 * 2 * 16
+                     : mode == SCAN_NN    ? 4 * scan_qt(a.ix.row_bytes / 64) * 16
+                                          : 4 * range_qt(a.ix.row_bytes / 32) * 32;
+    const bool range_int = a.ix.dtype != RR_F32 && mode == SCAN_RANGE;
+    const int tile = range_int ? range_tile(a.ix.row_bytes / 32) : 16; // base points
     const int64_t qblocks = (a.nq + qper - 1) / qper;
     // enough workgroups to fill the machine several times over
     int64_t target = 4096;
     int64_t pblocks = std::max<int64_t>(1, target / std::max<int64_t>(qblocks, 1));
-    a.chunk = ((a.ix.n + pblocks - 1) / pblocks + 15) / 16 * 16;
+    a.chunk = ((a.ix.n + pblocks - 1) / pblocks + tile - 1) / tile * tile;
     pblocks = (a.ix.n + a.chunk - 1) / a.chunk;
     if (pblocks > 65535) {
         pblocks = 65535;
-        a.chunk = ((a.ix.n + pblocks - 1) / pblocks + 15) / 16 * 16;
+        a.chunk = ((a.ix.n + pblocks - 1) / pblocks + tile - 1) / tile * tile;
         pblocks = (a.ix.n + a.chunk - 1) / a.chunk;
     }
+    a.qblocks = (int32_t)qblocks;
     dim3 grid((unsigned)qblocks, (unsigned)pblocks), block(256);
     const bool ip = a.ix.metric == RR_IP;
     if (a.ix.dtype == RR_F32) {
@@ -432,8 +588,8 @@ static hipError_t launch_scan(const ScanArgs &a0, int mode, hipStream_t s) {
     const int ks = a.ix.row_bytes / 64;
 #define RR_SCAN_KS(K)                                                                         \
     if (ks == K) {                                                                            \
-        if (mode == SCAN_NN) launch_scan_int<K, SCAN_NN>(a, ip, grid, block, s);                 \
-        else launch_scan_int<K, SCAN_RANGE>(a, ip, grid, block, s);                                \
+        if (mode == SCAN_NN) launch_scan_int<K>(a, ip, grid, block, s);                         \
+        else launch_scan_range<2 * K>(a, ip, dim3((unsigned)(qblocks * ((pblocks + 7) / 8 * 8))), block, s); \
         return hipGetLastError();                                                             \
     }
     RR_SCAN_KS(1) RR_SCAN_KS(2) RR_SCAN_KS(3) RR_SCAN_KS(4) RR_SCAN_KS(6) RR_SCAN_KS(8)
