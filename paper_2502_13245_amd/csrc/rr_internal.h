@@ -131,8 +131,9 @@ struct SearchBufs {
     unsigned long long *hash = nullptr; // [hash_cap] (task << 32 | id), ~0 = empty
     int64_t hash_cap = 0;
     // per-task membership bitmaps for tasks below bm_tasks (each task's words
-    // are cleared by the beam kernel when it creates the task); tasks at or
-    // above bm_tasks use the hash table
+    // are cleared by the beam kernel when it creates the task, or written by the
+    // task-local kernel when it hands the task on); tasks at or above bm_tasks
+    // use the hash table
     uint32_t *bm = nullptr;     // [bm_tasks][bm_words]
     int64_t bm_words = 0;       // 32-bit words per task: n bits rounded up to 128
     int64_t bm_tasks = 0;

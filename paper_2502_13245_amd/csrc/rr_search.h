@@ -5,10 +5,11 @@
 // the d_visited early stop (Algorithm 5).  Queries come from a device-side
 // atomic queue, so a grid sized to the machine drains any batch.  Queries
 // whose in-range beam reaches the expansion threshold (Algorithm 6) become
-// tasks of the greedy phase (Algorithm 2), which a cooperative grid runs
-// level by level over all tasks at once: the closure inside the ball does
+// tasks of the greedy phase (Algorithm 2).  The closure inside the ball does
 // not depend on visiting order, so every frontier node of every query is an
-// independent work item and heavy queries spread over the whole GPU.
+// independent work item: where the set of a task fits in LDS one workgroup
+// runs a task, and a cooperative grid runs the rest, and the large balls
+// handed on, level by level over all tasks at once.
 //
 // Exactness of the beam on a GPU rests on two facts about Algorithm 1 under
 // the total order (d, id):
