@@ -1133,8 +1133,8 @@ __global__ void k_scan_add(int64_t *out, int64_t n, const int64_t *tile_sum) {
 // The same scan by one workgroup, SCAN_ONE_TILE counts at a time.  Bound by
 // latency: the three launches above take 4.6 us each at any small size, and
 // two gaps between them; this one takes 11.5 us at 10,000 counts (two tiles)
-// and one launch.  From a third tile on the kernels above are the faster ones,
-// since they scan the tiles side by side.  One-query call about 10 us shorter.
+// and one launch.  At that 6 us a tile a third one would pass what the kernels
+// above take, which scan the tiles side by side.
 constexpr int SCAN_ONE_BLOCK = 1024;
 constexpr int64_t SCAN_ONE_TILE = SCAN_ONE_BLOCK * SCAN_ITEMS;
 constexpr int64_t SCAN_ONE_MAX = 2 * SCAN_ONE_TILE;
