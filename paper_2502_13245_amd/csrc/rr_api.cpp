@@ -778,16 +778,10 @@ rr_status rr::prepare_search(const rr_index *ix, const rr_search_params *sp, Sea
     if (cs & (cs - 1)) return fail(RR_EINVAL, "cache_slots must be a power of two");
     if (cs < 64 || cs > 16384) return fail(RR_EINVAL, "cache_slots must be in [64, 16384]");
     cfg.cache_slots = cs;
-    // doubling: the widest round is the first beam * 2^k >= max_beam, and
-    // its beam lives in LDS
-    int64_t bcap = sp->beam;
-    if (doubling)
-        while (bcap < sp->max_beam && bcap < (1 << 20)) bcap *= 2;
-    // LDS per wave: B (keys and ids; doubling keeps two copies, the beam
-    // kernel merges in place), 64 candidates, the visited cache
-    const size_t per_wave = (size_t)(doubling ? 2 : 1) * (ix->dtype == RR_F32 ? 12 : 8) * bcap +
-                            64 * 12 + cs * 4 + 128;
-    const size_t lds_cap = 160 * 1024;
+    // doubling: the beam of the widest round lives in LDS
+    const int64_t bcap = doubling ? doubling_width(sp->beam, sp->max_beam) : sp->beam;
+    const size_t per_wave = search_lds_bytes(doubling, bcap, cs, ix->dtype == RR_F32 ? 12 : 8);
+    const size_t lds_cap = LDS_PER_CU;
     if (per_wave > lds_cap) {
         if (doubling)
             return fail(RR_EINVAL, "max_beam: a doubling round of width %lld does not fit the LDS of "

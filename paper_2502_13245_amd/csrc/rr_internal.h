@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "rr.h"
+#include "rr_plan.h"
 
 namespace rr {
 

@@ -1,0 +1,34 @@
+// rr_plan.h -- sizes that the host plans and the kernels rely on.  Plain C++,
+// so that tests of these rules compile it for the CPU alone.
+#pragma once
+
+#include <cstddef>
+#include <cstdint>
+
+namespace rr {
+
+// LDS of one wave of the beam and doubling kernels: scratch keys, the beam's
+// array of bcap keys, the seen cache of cs ids.  A key takes key_bytes (8, or
+// 12 for FP64 distances).  The scratch holds 64 keys, or 64-bit words with one
+// bit for every key of the array (WaveBeam::merge_side).
+constexpr int32_t beam_scratch_keys(int32_t bcap) { return bcap > 4096 ? (bcap + 63) / 64 : 64; }
+constexpr int32_t wave_lds_bytes(int32_t bcap, int32_t cs, int32_t key_bytes) {
+    return (((bcap + beam_scratch_keys(bcap)) * key_bytes + 15) & ~15) + cs * 4;
+}
+
+// What a search is admitted by, never less than wave_lds_bytes.  For doubling
+// it counts the beam twice, more than the kernel holds: the widths that are
+// taken, and the waves of a workgroup, follow from it.
+constexpr size_t LDS_PER_CU = 160 * 1024;
+constexpr size_t search_lds_bytes(bool doubling, int64_t bcap, int32_t cs, int32_t key_bytes) {
+    return (size_t)(doubling ? 2 : 1) * key_bytes * bcap + 64 * 12 + cs * 4 + 128;
+}
+
+// doubling: the widest round is the first beam * 2^k >= max_beam
+constexpr int64_t doubling_width(int64_t beam, int64_t max_beam) {
+    int64_t b = beam;
+    while (b < max_beam && b < (1 << 20)) b *= 2;
+    return b;
+}
+
+} // namespace rr

@@ -825,7 +825,7 @@ template <typename D> struct WaveBeam {
     static constexpr bool WIDE_KEY = sizeof(D) == 8;
     uint64_t *mv; // main, in LDS: the keys, or the distances of FP64 keys
     uint32_t *mi; // FP64 keys: their second words
-    uint64_t *xv; // scratch keys, laid out the same
+    uint64_t *xv; // scratch keys, laid out the same (first, the ids of a visit's candidates)
     uint32_t *xi;
     int b;
     K side;       // this lane's key
@@ -874,11 +874,9 @@ template <typename D> struct WaveBeam {
         return r;
     }
 
-    // scratch: 64 keys, and a bit for every key of main
-    static __host__ __device__ __forceinline__ int scratch_keys(int bcap) { return bcap > 4096 ? bcap / 64 : 64; }
-    // lds: scratch_keys(bcap) + bcap keys
+    // lds: wave_lds_bytes of bcap keys
     __device__ __forceinline__ void init(uint8_t *lds, int bcap, int width) {
-        const int sk = scratch_keys(bcap);
+        const int sk = beam_scratch_keys(bcap);
         xv = reinterpret_cast<uint64_t *>(lds);
         mv = xv + sk;
         xi = reinterpret_cast<uint32_t *>(mv + bcap);
@@ -1140,12 +1138,8 @@ template <typename D> struct WaveBeam {
     }
 };
 
-// LDS of one wave: scratch (which also holds the ids of a visit's candidates
-// until their keys are made), main, the seen cache
-template <typename D>
-__host__ __device__ inline int32_t wave_lds_bytes(int32_t bcap, int32_t cs) {
-    return (((bcap + WaveBeam<D>::scratch_keys(bcap)) * (sizeof(D) == 8 ? 12 : 8) + 15) & ~15) + cs * 4;
-}
+// LDS bytes of a beam key: 32-bit distances in one word, FP64 ones in two
+template <typename D> constexpr int32_t beam_key_bytes() { return sizeof(D) == 8 ? 12 : 8; }
 
 // --------------------------------------------------------------------------
 // beam kernel: Algorithm 1 (+ Algorithm 5), then Algorithm 6's decision
@@ -2638,7 +2632,7 @@ static hipError_t run_beam(const DevIndex &ix, int64_t nq, const SearchCfg &cfg,
     a.probe_f = sl.probe_f;
     nq = a.nwork;
     a.bcap = cfg.beam;
-    a.lds_per_wave = wave_lds_bytes<D>(cfg.beam, cfg.cache_slots);
+    a.lds_per_wave = wave_lds_bytes(cfg.beam, cfg.cache_slots, beam_key_bytes<D>());
     const int waves = cfg.waves;
     const size_t shmem = (size_t)a.lds_per_wave * waves;
     auto kern = k_beam<DTYPE, CPL, G>;
@@ -2707,7 +2701,7 @@ static hipError_t run_doubling(const DevIndex &ix, int64_t nq, const SearchCfg &
     a.sb = sb;
     a.nq = nq;
     a.bcap = cfg.bcap;
-    a.lds_per_wave = wave_lds_bytes<D>(cfg.bcap, cfg.cache_slots);
+    a.lds_per_wave = wave_lds_bytes(cfg.bcap, cfg.cache_slots, beam_key_bytes<D>());
     a.s_pool = (uint8_t *)s_pool;
     a.s_cap = s_cap;
     const int waves = cfg.waves;
