@@ -31,4 +31,18 @@ constexpr int64_t doubling_width(int64_t beam, int64_t max_beam) {
     return b;
 }
 
+// The list of a task inside one workgroup (k_greedy_local) is stopped this far
+// from its end.  `open`: seeds that are not finished, drawn or not, read before
+// the wave adds its points.  Let P be the end of the last addition that did not
+// stop the list.  After P a wave adds the neighbours of the point it is at, 64 at
+// most, and with that it stops the list itself; from then on it expands seeds
+// only, and these were all open when P's wave read the count.  So the list ends
+// at P + 64 (waves + open) at most.
+constexpr int local_margin(int waves, int open) { return (waves + open) * 64; }
+constexpr int LOCAL_SEEDS = 32;   // tasks with more seeds start in the level kernel
+constexpr int LOCAL_WAVES = 16;   // waves of a workgroup at most
+constexpr int LOCAL_LIST = 8192;  // found points a workgroup can hold at most
+// the shortest list worth its start
+constexpr int LOCAL_LEAST = local_margin(LOCAL_WAVES, LOCAL_SEEDS) + 256;
+
 } // namespace rr

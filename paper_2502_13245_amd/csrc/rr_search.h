@@ -2347,13 +2347,8 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
 // points 13.1 -> 6.0 ms; 100K x 768 8-bit pass, 45K points 1.16 -> 0.56 ms.
 // Handing on at a backlog of 384 or 1,024 points took 1 and 4% longer on the
 // first, at an idle half or quarter of the workgroups 5 and 9%.
-constexpr int LOCAL_SEEDS = 32;      // tasks with more seeds start in the level kernel
-constexpr int LOCAL_LIST = 8192;     // found points a workgroup can hold at most
 constexpr int LOCAL_IDLE = 6;        // eighths of the workgroups out of tasks, and
 constexpr int LOCAL_BACKLOG = 192;   // points waiting, from which the level kernel is worth its start
-// the list is stopped this far from its end: every wave may still add the
-// neighbours of the point it is at, and so may every seed not yet taken
-constexpr int local_margin(int waves, int seeds) { return (waves + seeds) * 64; }
 
 // Whether the task-local kernel runs, with how many workgroups and how long a
 // list each (a list's distances lie in the finalization's item_cap entries,
@@ -2361,8 +2356,8 @@ constexpr int local_margin(int waves, int seeds) { return (waves + seeds) * 64; 
 // list some way above the margin, and a workgroup for every CU or query.
 inline void plan_local(SearchBufs &sb, int64_t n, int64_t nq, int num_cus) {
     sb.local_grid = sb.local_cap = 0;
-    const int64_t words = bitmap_words(n), least = local_margin(16, LOCAL_SEEDS) + 256;
-    const int64_t lds = 160 * 1024, fix = words * 4 + 16 * 64 * 8 + 512;
+    const int64_t words = bitmap_words(n), least = LOCAL_LEAST;
+    const int64_t lds = 160 * 1024, fix = words * 4 + LOCAL_WAVES * 64 * 8 + 512;
     if (nq <= 0 || fix + least * 4 > lds) return;
     const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(4, lds / (fix + LOCAL_LIST * 4)));
     const int64_t grid = std::min(std::min(nq, per_cu * num_cus), sb.item_cap / least);
@@ -2375,7 +2370,7 @@ inline void plan_local(SearchBufs &sb, int64_t n, int64_t nq, int num_cus) {
 
 struct LocalTask {
     int head, tail, done, stop; // tickets given, points found, points finished
-    int task, ns, nd, cs, cd;
+    int task, ns, seeds, cs, cd; // seeds: of the points finished
     unsigned evals, rechk;
     unsigned long long base_d, base_s;
     long long keep_d, keep_s;
@@ -2403,7 +2398,7 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
     uint32_t *const ci = bm + words + cap + wid * 64;
     uint32_t *const xi = bm + words + cap + (GW + wid) * 64; // approximate passes
     LocalTask &T = *reinterpret_cast<LocalTask *>(bm + words + cap + (dapprox(DTYPE) ? 2 : 1) * GW * 64);
-    volatile int *const v_head = &T.head, *const v_tail = &T.tail, *const v_done = &T.done, *const v_stop = &T.stop;
+    volatile int *const v_tail = &T.tail, *const v_done = &T.done, *const v_seeds = &T.seeds, *const v_stop = &T.stop;
     const DevIndex &ix = a.ix;
     const int R = ix.R;
     const int64_t ntasks = (int64_t)a.sb.counters[CTR_TASKS];
@@ -2418,7 +2413,7 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
             T.task = (int)atomicAdd(queue, 1ull);
             T.head = T.tail = T.done = T.stop = 0;
             T.evals = T.rechk = 0u;
-            T.ns = T.nd = T.cs = T.cd = 0;
+            T.ns = T.seeds = T.cs = T.cd = 0;
         }
         __syncthreads();
         const int t = __builtin_amdgcn_readfirstlane(T.task);
@@ -2514,22 +2509,24 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
                 const unsigned long long im = __ballot(in);
                 if (im) {
                     const int m = __popcll(im);
+                    // (read before the points are added: local_margin)
+                    const int open = nseed - __builtin_amdgcn_readfirstlane(*v_seeds);
+                    wave_sync();
                     int pos = 0;
                     if (lane == 0) pos = atomicAdd(&T.tail, m);
                     pos = __builtin_amdgcn_readfirstlane(pos);
-                    // (this wave's points are in; a seed taken after `head` is
-                    // read is counted all the same)
-                    if (pos + m > cap - local_margin(GW, max(0, nseed - *v_head)) && lane == 0) *v_stop = 1;
+                    if (pos + m > cap - local_margin(GW, open) && lane == 0) *v_stop = 1;
                     const int o = pos + mbcnt(im);
                     if (in) {
                         sc[o] = d;
-                        ids[o] = id; // (o < cap: the margin)
+                        ids[o] = id; // (o < cap: local_margin)
                     }
                 }
             }
             wave_sync();
             if (lane == 0) {
                 if (i >= nseed) ids[i - nseed] = p | 0x80000000u; // expanded
+                else atomicAdd(&T.seeds, 1);
                 atomicAdd(&T.done, 1);
             }
             i = ni;

@@ -2,9 +2,12 @@
 // values that the library accepts.  Prints what is wrong; exit status 1 then.
 // Test infrastructure only.
 //
-// usage: plan_driver lds
+// usage: plan_driver lds | list | list-drawn
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <random>
+#include <vector>
 
 #include "rr_plan.h"
 
@@ -38,9 +41,82 @@ static long lds() {
     return seen;
 }
 
+// The list of k_greedy_local: its waves as step machines (every step one access
+// of the shared counters), run in random orders in which some waves stall for
+// long, with up to 64 points found at each expansion.  No list may pass its
+// capacity, and every task ends.  `drawn`: the margin counts the seeds whose
+// tickets are not drawn yet (a wave draws its next ticket before it adds the
+// points it found), which the orders must be able to tell.
+static long list(bool drawn) {
+    std::mt19937 g(5);
+    long seen = 0, over = 0;
+    for (int run = 0; run < 800; ++run) {
+        const int GW = 1 + (int)(g() % LOCAL_WAVES), nseed = (int)(g() % (LOCAL_SEEDS + 1));
+        const int cap = LOCAL_LEAST + (run % 3 ? 0 : (int)(g() % (LOCAL_LIST - LOCAL_LEAST))) / 4 * 4;
+        int head = 0, tail = 0, done = 0, seeds = 0, top = 0;
+        bool stop = false;
+        std::vector<char> there(cap + 128 * LOCAL_WAVES, 0);
+        struct W { int pc = 0, i = 0, ni = 0, m = 0, pos = 0, open = 0, stall = 0; };
+        std::vector<W> w(GW);
+        // waves that stall, and where: before they add the points of a seed
+        const int slow = (int)(g() % (GW + 1)), few = (int)(g() % 4);
+        for (auto &x : w) x.i = head++;
+        int left = GW, steps = 0;
+        for (; left > 0 && steps < 4000000; ++steps) {
+            const int k = (int)(g() % GW);
+            W &x = w[k];
+            if (x.pc == 6 || (x.stall > 0 && x.stall--)) continue;
+            switch (x.pc) {
+            case 0: // the ticket's point
+                if (x.i < nseed) { x.pc = 1; break; }
+                if (stop) { x.pc = 6; --left; break; }
+                if (x.i - nseed < tail && there[x.i - nseed]) { x.pc = 1; break; }
+                if (done == nseed + tail) { x.pc = 6; --left; }
+                break;
+            case 1: // the next ticket, then the neighbours
+                x.ni = head++;
+                x.m = few ? 64 : (int)(g() % 65);
+                x.pc = 2;
+                if (k < slow && x.i < nseed) x.stall = 20000;
+                break;
+            case 2:
+                x.open = nseed - seeds;
+                x.pc = 3;
+                break;
+            case 3:
+                x.pos = tail;
+                tail += x.m;
+                x.pc = 4;
+                if (g() % 8 == 0) x.stall = (int)(g() % 400);
+                break;
+            case 4:
+                if (drawn) x.open = std::max(0, nseed - head);
+                if (x.m && x.pos + x.m > cap - local_margin(GW, x.open)) stop = true;
+                for (int j = 0; j < x.m && x.pos + j < (int)there.size(); ++j) there[x.pos + j] = 1;
+                top = std::max(top, x.pos + x.m);
+                x.pc = 5;
+                break;
+            default: // finished
+                if (x.i < nseed) ++seeds;
+                ++done;
+                x.i = x.ni;
+                x.pc = 0;
+            }
+        }
+        ++seen;
+        over += top > cap;
+        EXPECT(top <= cap, "waves %d seeds %d: %d points in a list of %d\n", GW, nseed, top, cap);
+        EXPECT(left == 0, "waves %d seeds %d: not ended\n", GW, nseed);
+    }
+    std::printf("%ld lists passed their capacity\n", over);
+    return seen;
+}
+
 int main(int argc, char **argv) {
     long seen = 0;
     if (argc > 1 && !std::strcmp(argv[1], "lds")) seen = lds();
+    if (argc > 1 && !std::strcmp(argv[1], "list")) seen = list(false);
+    if (argc > 1 && !std::strcmp(argv[1], "list-drawn")) seen = list(true);
     std::printf("%ld checked, %d wrong\n", seen, bad);
     return bad || !seen;
 }

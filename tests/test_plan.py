@@ -26,3 +26,11 @@ def driver(tmp_path_factory):
 def test_beam_scratch_and_lds(driver):
     rc, out = driver("lds")
     assert rc == 0, out
+
+
+def test_task_list_stays_in_its_capacity(driver):
+    rc, out = driver("list")
+    assert rc == 0, out
+    # a margin that leaves out the seeds already drawn is told apart
+    rc, out = driver("list-drawn")
+    assert rc == 1 and "points in a list" in out
