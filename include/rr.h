@@ -169,12 +169,14 @@ typedef struct {
     double beam_ms;            /* with timing: beam kernel (event pair)     */
     double greedy_ms;          /* with timing: greedy phase incl. sort/emit */
     double total_ms;           /* with timing: whole search call            */
-    int64_t greedy_levels;     /* frontier levels run by the greedy phase   */
+    int64_t greedy_levels;     /* frontier levels of the greedy phase; the task-
+                                  local kernel counts as level 1, however deep  */
     int64_t greedy_items;      /* frontier items (in-ball points) processed */
     int64_t bytes_greedy;      /* algorithmic bytes of the greedy phase     */
     double greedy_kernel_ms;   /* with timing: greedy kernel alone          */
-    int64_t greedy_set_ops;    /* greedy phase: updates of the global (query,
-                                  point) set after the workgroup caches       */
+    int64_t greedy_set_ops;    /* greedy phase: updates of the (query, point)
+                                  set in memory after the workgroup caches (the
+                                  task-local kernel's set, in LDS, has none)  */
 } rr_batch_stats;
 
 const char *rr_last_error(void);
@@ -511,7 +513,11 @@ rr_status rr_results_stats(const rr_results *res, rr_query_stats *per_query_host
  * for each level l < min(max_levels, *n_levels) of the level-synchronous
  * expansion, items[l] = points expanded, expand_ms[l] = time to expand
  * them, regroup_ms[l] = time to group the next level by task (wall-clock
- * stamps taken inside the kernel).  Any output pointer may be NULL.
+ * stamps taken inside the kernels).  Where tasks are expanded inside single
+ * workgroups first (up to about 1.1M points), level 0 holds every seed and
+ * level 1 the points found there, without levels: expand_ms[1] is that
+ * kernel's time, expand_ms[0] that of the seeds left to the level-synchronous
+ * expansion, which goes on with level 2.  Any output pointer may be NULL.
  * *n_levels = 0 if no greedy phase ran.  Synchronizes with the stream. */
 rr_status rr_results_level_profile(const rr_results *res, int32_t max_levels, int64_t *items,
                                    double *expand_ms, double *regroup_ms, int32_t *n_levels);

@@ -1402,10 +1402,13 @@ extern "C" rr_status rr_results_level_profile(const rr_results *res, int32_t max
     unsigned long long prev = clk[0];
     for (int32_t l = 0; l < n; ++l) {
         const unsigned long long a = clk[1 + 3 * l], c = clk[3 + 3 * l];
+        const bool local = l == 1 && res->sb.local_grid > 0;
+        const unsigned long long b = local ? a : prev, e = local ? clk[0] : a; // of the expansion
         if (items) items[l] = (int64_t)lc[l];
-        if (expand_ms) expand_ms[l] = a >= prev ? (double)(a - prev) * ms_per_tick : 0.0;
-        if (regroup_ms) regroup_ms[l] = c >= a && c ? (double)(c - a) * ms_per_tick : 0.0;
-        prev = c ? c : a;
+        // (a stamp of 0: the level kernel had nothing to expand there)
+        if (expand_ms) expand_ms[l] = a && e >= b ? (double)(e - b) * ms_per_tick : 0.0;
+        if (regroup_ms) regroup_ms[l] = !local && c && c >= a ? (double)(c - a) * ms_per_tick : 0.0;
+        if (!local && a) prev = c ? c : a;
     }
     *n_levels = n;
     return RR_OK;

@@ -1980,7 +1980,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
     };
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < 1 + 3 * LEVEL_CLOCKS; i += blockDim.x)
-            a.sb.level_clock[i] = i == 0 ? wall_clock64() : 0ull;
+            if (i != LOCAL_CLOCK || a.sb.local_grid == 0) a.sb.level_clock[i] = i == 0 ? wall_clock64() : 0ull;
     int64_t base = 0;
     int lvl = 0;
     bool grouped = true;
@@ -2407,6 +2407,7 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
     O *const sc = (O *)a.sb.seg_dists + (int64_t)blockIdx.x * cap; // the list's distances
     unsigned long long *const queue = &a.sb.counters[CTR_LOCAL_QUEUE];
     const int64_t idle = (int64_t)gridDim.x * LOCAL_IDLE / 8;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.sb.level_clock[LOCAL_CLOCK] = wall_clock64();
 
     for (;;) {
         if (threadIdx.x == 0) {

@@ -434,7 +434,8 @@ class PendingResults:
 
     def level_profile(self, max_levels=64):
         """Per level of the greedy phase: points expanded and the time spent
-        expanding them and regrouping the next level (ms)."""
+        expanding them and regrouping the next level (ms); level 1 is the
+        kernel that expands whole tasks, where that one ran."""
         items = (C.c_int64 * max_levels)()
         exp_ms = (C.c_double * max_levels)()
         reg_ms = (C.c_double * max_levels)()
