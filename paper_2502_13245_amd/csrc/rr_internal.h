@@ -115,7 +115,6 @@ struct SearchBufs {
     unsigned long long *task_evals = nullptr; // [nq]
     unsigned long long *task_rechk = nullptr; // [nq] exact rechecks in the band
     int8_t *task_expand = nullptr;            // [nq] 1: run Algorithm 2 from the seeds; 2: seeds expanded
-    int64_t *task_seed = nullptr;             // [nq] first of the task's seeds among the items
     int8_t *task_trunc = nullptr;             // [nq] 1: a capacity dropped some of the task's results
     const uint8_t *deg = nullptr; // [n] out-degrees (greedy visits' adjacency entries); null: not counted
     unsigned long long *task_prev = nullptr;  // [nq] task_cnt before the current level
@@ -143,7 +142,8 @@ struct SearchBufs {
     int32_t local_grid = 0, local_cap = 0;
     int64_t *seg_off = nullptr;   // [nq + 1] per-task segment offsets
     unsigned long long *seg_cur = nullptr;   // [nq]
-    int64_t *task_out = nullptr;  // [nq] arena offset of each task's sorted list (finalization)
+    int64_t *task_out = nullptr;  // [nq] arena offset of each task's sorted list (finalization); before
+                                  // that, the first of the task's seeds among the items
     int32_t *task_long = nullptr; // [nq] tasks of more than 64 items, longest size class first
     int32_t *seg_ids = nullptr;   // [item_cap]
     void *seg_dists = nullptr;
@@ -187,11 +187,12 @@ enum {
     CTR_LONG_TASKS = 32 * CTR_STRIDE,  // finalization: tasks a whole workgroup sorts
     CTR_SORT_QUEUE = 33 * CTR_STRIDE,  // finalization: next of them to sort
     CTR_MID_TASKS = 34 * CTR_STRIDE,   // finalization: tasks one wave sorts in LDS
-    CTR_LOCAL_QUEUE = 35 * CTR_STRIDE, // greedy phase, task-local kernel: next task
-    CTR_LOCAL_ITEMS = 36 * CTR_STRIDE, // items it emitted or handed on
-    CTR_SPILL = 37 * CTR_STRIDE,       // of these, unexpanded ones handed to the level kernel
-    CTR_LEFT = 38 * CTR_STRIDE,        // tasks left to the level kernel from their seeds on
-    CTR_COUNT = 39 * CTR_STRIDE
+    // the task-local kernel's, on lines that later kernels count on
+    CTR_LOCAL_QUEUE = CTR_SORT_QUEUE + 1,  // next task
+    CTR_LOCAL_ITEMS = CTR_LONG_TASKS + 1,  // items it emitted or handed on
+    CTR_SPILL = CTR_MID_TASKS + 1,         // of these, unexpanded ones handed to the level kernel
+    CTR_LEFT = CTR_LEVELS + 1,             // tasks left to the level kernel from their seeds on
+    CTR_COUNT = 35 * CTR_STRIDE
 };
 
 // kernel launchers (rr_kernels.hip)

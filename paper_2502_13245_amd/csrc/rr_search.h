@@ -1480,7 +1480,7 @@ __global__ __launch_bounds__(512, (beam_waves<DTYPE, CPL>())) void k_beam(BeamAr
                 a.sb.task_evals[t] = 0ull;
                 a.sb.task_rechk[t] = 0ull;
                 a.sb.task_expand[t] = expand ? 1 : 0;
-                a.sb.task_seed[t] = off;
+                a.sb.task_out[t] = off;
                 a.sb.res_off[q] = 0;
                 a.sb.res_cnt[q] = 0;
             }
@@ -2431,7 +2431,7 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
             __syncthreads(); // T is written again
             continue;
         }
-        const int64_t seed0 = a.sb.task_seed[t];
+        const int64_t seed0 = a.sb.task_out[t];
         const int32_t q = __builtin_amdgcn_readfirstlane(a.sb.task_q[t]);
         for (int64_t i = threadIdx.x; i < words / 4; i += blockDim.x)
             reinterpret_cast<uint4 *>(bm)[i] = make_uint4(0u, 0u, 0u, 0u);
