@@ -437,9 +437,10 @@ extern "C" rr_status rr_index_to_device(rr_index *ix, const rr_allocator *alloc,
             hn[(size_t)i] = (float)(0.5 * nn);
         }
         ix->d_norm = ix->alloc.alloc(hn.size() * sizeof(float));
-        if (!ix->d_norm) return fail(RR_ENOMEM, "device allocation failed");
-        HIP_TRY(hipMemcpyAsync(ix->d_norm, hn.data(), hn.size() * sizeof(float), hipMemcpyHostToDevice, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        if (ix->d_norm) { // (without it the dense scans run in FP64 alone)
+            HIP_TRY(hipMemcpyAsync(ix->d_norm, hn.data(), hn.size() * sizeof(float), hipMemcpyHostToDevice, s));
+            HIP_TRY(hipStreamSynchronize(s));
+        }
         ix->d_bf16 = ix->alloc.alloc(h.size() * 2);
         if (!ix->d_bf16) return fail(RR_ENOMEM, "device allocation failed");
         HIP_TRY(hipMemcpyAsync(ix->d_bf16, h.data(), h.size() * 2, hipMemcpyHostToDevice, s));
@@ -1075,8 +1076,16 @@ static rr_status brute_force_once(const rr_index *ix, const void *queries_dev, i
     rr_default_search_params(&sp);
     const int64_t item_cap = std::max<int64_t>(cap, 1);
     rr_results *res = nullptr;
+    // the float scan's scratch follows the padded queries; where there is no
+    // room for it the FP64 scan runs, which needs none
+    int64_t ws_row = scan_ws_row(ix->dev);
     rr_status st = make_results(ix, ix->dev, nq, &sp, true, item_cap, item_cap, 1024,
-                                ix->dev.row_bytes + (int32_t)scan_ws_row(ix->dev), alloc, stream, &res);
+                                ix->dev.row_bytes + (int32_t)ws_row, alloc, stream, &res);
+    if (st == RR_ENOMEM && ws_row > 0) {
+        ws_row = 0;
+        st = make_results(ix, ix->dev, nq, &sp, true, item_cap, item_cap, 1024, ix->dev.row_bytes, alloc,
+                          stream, &res);
+    }
     if (st != RR_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     SearchBufs &sb = res->sb;
@@ -1097,9 +1106,8 @@ static rr_status brute_force_once(const rr_index *ix, const void *queries_dev, i
     HIP_TRY_R(launch_fill_u64(sb.counters, CTR_COUNT, 0ull, s));
     HIP_TRY_R(launch_fill_u64(sb.level_cnt, sb.max_levels, 0ull, s));
     HIP_TRY_R(launch_prep_queries(ix->dev, queries_dev, nq, radius, radius_dev, cfg, sb, s));
-    // the scan's scratch follows the padded queries
-    HIP_TRY_R(launch_brute_force(ix->dev, sb.qpad, sb.qth, nq, sb, sb.qpad + nq * ix->dev.row_bytes,
-                                 device_cus(), s));
+    HIP_TRY_R(launch_brute_force(ix->dev, sb.qpad, sb.qth, nq, sb,
+                                 ws_row > 0 ? sb.qpad + nq * ix->dev.row_bytes : nullptr, device_cus(), s));
     // the hit count decides whether the capacity sufficed (ground truth is
     // not on a timed path, so this call synchronizes)
     unsigned long long h = 0;
@@ -1288,18 +1296,24 @@ extern "C" rr_status rr_nn_dist(const rr_index *ix, const void *queries_dev, int
     rr::Allocator al = ix->alloc;
     al.stream = stream;
     const size_t qrows = (size_t)nq * ix->dev.row_bytes;
-    const size_t qbytes = qrows + (size_t)nq * scan_ws_row(ix->dev); // the scan's scratch follows
-    const size_t tbytes = ((qbytes + 255) & ~(size_t)255) + (size_t)nq * (sizeof(QThresh) + 8) + 512;
-    uint8_t *tmp = (uint8_t *)al.alloc(tbytes);
+    // the float scan's scratch follows the queries, as in brute_force_once
+    size_t ws = (size_t)nq * scan_ws_row(ix->dev);
+    auto rows_end = [&]() { return (qrows + ws + 255) & ~(size_t)255; };
+    auto bytes = [&]() { return rows_end() + (size_t)nq * (sizeof(QThresh) + 8) + 512; };
+    uint8_t *tmp = (uint8_t *)al.alloc(bytes());
+    if (!tmp && ws > 0) {
+        ws = 0;
+        tmp = (uint8_t *)al.alloc(bytes());
+    }
     if (!tmp) return fail(RR_ENOMEM, "device allocation failed");
     SearchBufs sb;
     sb.qpad = tmp;
-    sb.qth = (QThresh *)(tmp + ((qbytes + 255) & ~(size_t)255));
+    sb.qth = (QThresh *)(tmp + rows_end());
     unsigned long long *bits =
         (unsigned long long *)((uint8_t *)sb.qth + (((size_t)nq * sizeof(QThresh) + 255) & ~(size_t)255));
     SearchCfg cfg{};
     hipError_t e = launch_prep_queries(ix->dev, queries_dev, nq, 0.0, nullptr, cfg, sb, s);
-    if (e == hipSuccess) e = launch_nn_dist(ix->dev, sb.qpad, nq, nn_dev, bits, tmp + qrows, s);
+    if (e == hipSuccess) e = launch_nn_dist(ix->dev, sb.qpad, nq, nn_dev, bits, ws > 0 ? tmp + qrows : nullptr, s);
     if (e == hipSuccess && !al.has_user) e = hipStreamSynchronize(s);
     al.release(tmp);
     if (e != hipSuccess) return fail(RR_EHIP, "nn_dist: %s", hipGetErrorString(e));

@@ -241,7 +241,8 @@ hipError_t launch_results_copy(int dtype, int precision, const DevIndex &ix, con
                                int64_t capacity = INT64_MAX, bool scan_counts = true);
 size_t results_copy_tmp_bytes(int64_t nq);
 
-// brute force (rr_scan.hip); ws: scan_ws_row(ix) bytes of scratch per query
+// brute force (rr_scan.hip); ws: scan_ws_row(ix) bytes of scratch per query,
+// or null (float data then takes the FP64 scan)
 int64_t scan_ws_row(const DevIndex &ix);
 hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth,
                               int64_t nq, SearchBufs &sb, uint8_t *ws, int num_cus, hipStream_t s);

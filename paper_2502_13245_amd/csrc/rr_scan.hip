@@ -606,7 +606,7 @@ hipError_t launch_nn_dist(const DevIndex &ix, const uint8_t *qpad, int64_t nq, d
     a.nq = nq;
     a.nn_bits = bits;
     hipError_t e = hipSuccess;
-    if (scan_split_ok(ix)) {
+    if (ws && scan_split_ok(ix)) {
         e = launch_split_nn(a, ws, s);
     } else {
         e = launch_fill_u64(bits, nq, ~0ull, s);
@@ -639,7 +639,7 @@ hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QTh
     a.item_cursor = &sb.level_cnt[0];
     a.task_cnt = sb.task_cnt;
     a.overflow = &sb.counters[CTR_OVERFLOW];
-    return scan_split_ok(ix) ? launch_split_range(a, ws, s) : launch_scan(a, SCAN_RANGE, s);
+    return ws && scan_split_ok(ix) ? launch_split_range(a, ws, s) : launch_scan(a, SCAN_RANGE, s);
 }
 
 } // namespace rr
