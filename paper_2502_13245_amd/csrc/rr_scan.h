@@ -17,7 +17,8 @@ struct ScanArgs {
     const QThresh *qth;   // [nq] (range mode)
     int64_t nq;
     int64_t chunk;        // base points per workgroup
-    int32_t qblocks;      // query blocks (integer range scan)
+    int32_t qblocks;      // query blocks (integer range scan, split scan)
+    int32_t xcds;         // of scan_split
     // nn mode
     unsigned long long *nn_bits; // [nq] min distance bits (uint32 value or double bits)
     // range mode: hits appended as items (task = query)

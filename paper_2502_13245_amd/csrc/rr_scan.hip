@@ -254,14 +254,12 @@ __global__ __launch_bounds__(256, range_waves(KS)) void k_scan_range(ScanArgs a)
     constexpr int ROWS = TILE / PASS, COLS = CPR / TPR; // rows and chunks of a thread per step
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
-    // the query blocks of one chunk of the base follow each other on one XCD
-    // (workgroups are dealt to the 8 XCDs in turn), so its L2 serves them
-    const int64_t lin = blockIdx.x;
+    const int64_t lin = blockIdx.x; // (scan_split)
     // up to QT * 32 queries: every wave takes them all and a fourth of the points
     const bool few = a.nq <= QT * 32;
-    const int64_t q0 = few ? 0 : (((lin / 8) % a.qblocks) * 4 + wid) * (QT * 32);
+    const int64_t q0 = few ? 0 : (((lin / a.xcds) % a.qblocks) * 4 + wid) * (QT * 32);
     const int sub0 = few ? wid * 32 : 0, sub_step = few ? 128 : 32;
-    const int64_t p_begin = (lin % 8 + 8 * ((lin / 8) / a.qblocks)) * a.chunk;
+    const int64_t p_begin = (lin % a.xcds + a.xcds * (lin / a.xcds / a.qblocks)) * a.chunk;
     const int64_t p_end = min(a.ix.n, p_begin + a.chunk);
     if (p_begin >= p_end) return;
     const bool active = q0 < a.nq; // waves without queries only help to load
@@ -563,21 +561,37 @@ static hipError_t launch_scan(const ScanArgs &a0, int mode, hipStream_t s) {
                      : mode == SCAN_NN    ? 4 * scan_qt(a.ix.row_bytes / 64) * 16
                                           : 4 * range_qt(a.ix.row_bytes / 32) * 32;
     const bool range_int = a.ix.dtype != RR_F32 && mode == SCAN_RANGE;
-    const int tile = range_int ? range_tile(a.ix.row_bytes / 32) : 16; // base points
     const int64_t qblocks = (a.nq + qper - 1) / qper;
+    a.qblocks = (int32_t)qblocks;
+    dim3 block(256);
+    const bool ip = a.ix.metric == RR_IP;
+    const int ks = a.ix.row_bytes / 64;
+    if (range_int) {
+        const int tile = range_tile(2 * ks);
+        const ScanSplit sp = scan_split((a.ix.n + tile - 1) / tile, qblocks);
+        a.chunk = sp.chunk * tile;
+        a.xcds = sp.xcds;
+        const dim3 grid((unsigned)sp.groups(qblocks));
+#define RR_SCAN_KS(K)                                                                         \
+    if (ks == K) {                                                                            \
+        launch_scan_range<2 * K>(a, ip, grid, block, s);                                      \
+        return hipGetLastError();                                                             \
+    }
+        RR_SCAN_KS(1) RR_SCAN_KS(2) RR_SCAN_KS(3) RR_SCAN_KS(4) RR_SCAN_KS(6) RR_SCAN_KS(8)
+#undef RR_SCAN_KS
+        return hipErrorInvalidValue; // integer rows above 512 bytes are not scanned
+    }
     // enough workgroups to fill the machine several times over
     int64_t target = 4096;
     int64_t pblocks = std::max<int64_t>(1, target / std::max<int64_t>(qblocks, 1));
-    a.chunk = ((a.ix.n + pblocks - 1) / pblocks + tile - 1) / tile * tile;
+    a.chunk = ((a.ix.n + pblocks - 1) / pblocks + 15) / 16 * 16;
     pblocks = (a.ix.n + a.chunk - 1) / a.chunk;
     if (pblocks > 65535) {
         pblocks = 65535;
-        a.chunk = ((a.ix.n + pblocks - 1) / pblocks + tile - 1) / tile * tile;
+        a.chunk = ((a.ix.n + pblocks - 1) / pblocks + 15) / 16 * 16;
         pblocks = (a.ix.n + a.chunk - 1) / a.chunk;
     }
-    a.qblocks = (int32_t)qblocks;
-    dim3 grid((unsigned)qblocks, (unsigned)pblocks), block(256);
-    const bool ip = a.ix.metric == RR_IP;
+    dim3 grid((unsigned)qblocks, (unsigned)pblocks);
     if (a.ix.dtype == RR_F32) {
         if (ip && mode == SCAN_NN) hipLaunchKernelGGL((k_scan_f32<true, SCAN_NN>), grid, block, 0, s, a);
         else if (ip) hipLaunchKernelGGL((k_scan_f32<true, SCAN_RANGE>), grid, block, 0, s, a);
@@ -585,11 +599,9 @@ static hipError_t launch_scan(const ScanArgs &a0, int mode, hipStream_t s) {
         else hipLaunchKernelGGL((k_scan_f32<false, SCAN_RANGE>), grid, block, 0, s, a);
         return hipGetLastError();
     }
-    const int ks = a.ix.row_bytes / 64;
 #define RR_SCAN_KS(K)                                                                         \
     if (ks == K) {                                                                            \
-        if (mode == SCAN_NN) launch_scan_int<K>(a, ip, grid, block, s);                         \
-        else launch_scan_range<2 * K>(a, ip, dim3((unsigned)(qblocks * ((pblocks + 7) / 8 * 8))), block, s); \
+        launch_scan_int<K>(a, ip, grid, block, s);                                            \
         return hipGetLastError();                                                             \
     }
     RR_SCAN_KS(1) RR_SCAN_KS(2) RR_SCAN_KS(3) RR_SCAN_KS(4) RR_SCAN_KS(6) RR_SCAN_KS(8)

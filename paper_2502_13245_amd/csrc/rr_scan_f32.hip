@@ -59,8 +59,8 @@ struct SplitArgs {
     const uint16_t *qs;  // [nq][2][kpad] high and low parts of the queries
     const float *cinit;  // [nq] what the sums start from
     unsigned *best;      // [nq] SPLIT_MAX: ordered bits of the largest sum
-    int64_t pblocks;     // a multiple of 8
-    int32_t qblocks, kpad, cpl, g;
+    int64_t groups;      // workgroups
+    int32_t kpad, cpl, g;
 };
 
 __device__ __forceinline__ unsigned flt_order(float f) {
@@ -209,11 +209,9 @@ __global__ __launch_bounds__(256, 2) void k_scan_split(SplitArgs a) {
     double *st_d = reinterpret_cast<double *>(smem + 4 * PART * 16) + wid * SPLIT_STAGE;
     uint32_t *st_q = reinterpret_cast<uint32_t *>(smem + 4 * PART * 16 + 4 * SPLIT_STAGE * 8) + wid * 2 * SPLIT_STAGE;
     uint32_t *st_id = st_q + SPLIT_STAGE;
-    // the query blocks of one chunk of the base follow each other on one XCD
-    // (workgroups are dealt to the 8 XCDs in turn), so its L2 serves them
-    const int64_t lin = blockIdx.x;
-    const int64_t pb = lin % 8 + 8 * ((lin / 8) / a.qblocks);
-    const int64_t q0 = ((lin / 8) % a.qblocks) * SPLIT_Q + wid * 32;
+    const int64_t lin = blockIdx.x; // (scan_split)
+    const int64_t pb = lin % a.sc.xcds + a.sc.xcds * (lin / a.sc.xcds / a.sc.qblocks);
+    const int64_t q0 = ((lin / a.sc.xcds) % a.sc.qblocks) * SPLIT_Q + wid * 32;
     const int64_t p_begin = pb * a.sc.chunk, p_end = min(a.sc.ix.n, p_begin + a.sc.chunk);
     if (p_begin >= p_end) return;
     const bool active = q0 < a.sc.nq; // waves without queries only help to load
@@ -401,7 +399,7 @@ template <int KS, bool MULTI, int MODE> static hipError_t run_split(SplitArgs &a
     const hipError_t e = kernel_occupancy((const void *)kern, 256, shmem, &per_cu);
     if (e != hipSuccess) return e;
     if (per_cu < 1) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.qblocks * a.pblocks)), dim3(256), shmem, s, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.groups), dim3(256), shmem, s, a);
     return hipGetLastError();
 }
 
@@ -422,13 +420,11 @@ static hipError_t split_setup(const ScanArgs &sc, uint8_t *ws, SplitArgs &a, Spl
     a.best = w.best;
     a.kpad = split_kpad(sc.ix.d);
     row_split(sc.ix.row_bytes, &a.cpl, &a.g);
-    a.qblocks = (int32_t)((sc.nq + SPLIT_Q - 1) / SPLIT_Q);
-    // about 4,096 workgroups (512 are resident), a chunk of whole tiles each
-    int64_t pb = std::max<int64_t>(8, 4096 / a.qblocks);
-    const int64_t tiles = (sc.ix.n + SPLIT_TILE - 1) / SPLIT_TILE;
-    a.sc.chunk = (tiles + pb - 1) / pb * SPLIT_TILE;
-    pb = (sc.ix.n + a.sc.chunk - 1) / a.sc.chunk;
-    a.pblocks = (pb + 7) / 8 * 8;
+    a.sc.qblocks = (int32_t)((sc.nq + SPLIT_Q - 1) / SPLIT_Q);
+    const ScanSplit sp = scan_split((sc.ix.n + SPLIT_TILE - 1) / SPLIT_TILE, a.sc.qblocks);
+    a.sc.chunk = sp.chunk * SPLIT_TILE;
+    a.sc.xcds = sp.xcds;
+    a.groups = sp.groups(a.sc.qblocks);
     hipLaunchKernelGGL(k_split_prep, dim3((unsigned)((sc.nq + 3) / 4)), dim3(256), 0, s, sc.qpad, sc.qth, sc.nq,
                        sc.ix.row_bytes, sc.ix.d, a.kpad, (double)sc.ix.max_norm, (int)(sc.ix.metric == RR_IP),
                        w.qs, w.cinit, w.slack, w.best);

@@ -2,7 +2,7 @@
 // values that the library accepts.  Prints what is wrong; exit status 1 then.
 // Test infrastructure only.
 //
-// usage: plan_driver lds | list | list-drawn
+// usage: plan_driver lds | list | list-drawn | scan
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -112,10 +112,43 @@ static long list(bool drawn) {
     return seen;
 }
 
+// Dense scans: every tile of the base is taken once for every query block, and
+// no XCD has much more than the mean of the tiles (workgroup i runs on XCD i % 8)
+static long scan() {
+    long seen = 0;
+    std::vector<long> tiles = {1, 2, 7, 8, 9, 15, 16, 17, 63, 64, 65, 79, 100, 157, 782, 1000, 7813, 15625, 70313};
+    std::mt19937 g(9);
+    for (int i = 0; i < 300; ++i) tiles.push_back(1 + (long)(g() % (i < 150 ? 300 : 20000)));
+    for (long t : tiles)
+        for (long qb : {1l, 2l, 3l, 20l, 79l, 98l, 205l, 313l, 391l, 400l, 586l, 800l, 1954l, 7813l}) {
+            const ScanSplit s = scan_split(t, qb);
+            ++seen;
+            EXPECT(s.chunk >= 1 && s.chunks * s.chunk >= t && (s.chunks - 1) * s.chunk < t && (s.xcds == 1 || s.xcds == 8),
+                   "%ld tiles, %ld query blocks: chunks %ld of %ld\n", t, qb, (long)s.chunks, (long)s.chunk);
+            double load[8] = {0}, most = 0, all = 0;
+            std::vector<char> taken;
+            if (t * qb < 200000) taken.assign(t * qb, 0);
+            for (long lin = 0; lin < s.groups(qb); ++lin) {
+                const long p = lin % s.xcds + s.xcds * (lin / s.xcds / qb), q = lin / s.xcds % qb;
+                const long t0 = p * s.chunk, t1 = std::min<long>(t, t0 + s.chunk);
+                for (long k = t0; k < t1 && !taken.empty(); ++k) ++taken[k * qb + q];
+                if (t1 > t0) load[lin % 8] += t1 - t0;
+            }
+            for (double l : load) most = std::max(most, l), all += l;
+            EXPECT(all == (double)t * qb && std::all_of(taken.begin(), taken.end(), [](char c) { return c == 1; }),
+                   "%ld tiles, %ld query blocks: not every tile once\n", t, qb);
+            // (a last chunk for itself when workgroups are few)
+            EXPECT(most <= 1.1 * all / 8 + 2 * s.chunk, "%ld tiles, %ld query blocks: %g tiles on one XCD of %g\n", t, qb,
+                   most, all / 8);
+        }
+    return seen;
+}
+
 int main(int argc, char **argv) {
     long seen = 0;
     if (argc > 1 && !std::strcmp(argv[1], "lds")) seen = lds();
     if (argc > 1 && !std::strcmp(argv[1], "list")) seen = list(false);
+    if (argc > 1 && !std::strcmp(argv[1], "scan")) seen = scan();
     if (argc > 1 && !std::strcmp(argv[1], "list-drawn")) seen = list(true);
     std::printf("%ld checked, %d wrong\n", seen, bad);
     return bad || !seen;

@@ -34,3 +34,8 @@ def test_task_list_stays_in_its_capacity(driver):
     # a margin that leaves out the seeds already drawn is told apart
     rc, out = driver("list-drawn")
     assert rc == 1 and "points in a list" in out
+
+
+def test_dense_scans_load_the_xcds_evenly(driver):
+    rc, out = driver("scan")
+    assert rc == 0, out
