@@ -1076,13 +1076,13 @@ static rr_status brute_force_once(const rr_index *ix, const void *queries_dev, i
     rr_default_search_params(&sp);
     const int64_t item_cap = std::max<int64_t>(cap, 1);
     rr_results *res = nullptr;
-    // the float scan's scratch follows the padded queries; where there is no
-    // room for it the FP64 scan runs, which needs none
-    int64_t ws_row = scan_ws_row(ix->dev);
-    rr_status st = make_results(ix, ix->dev, nq, &sp, true, item_cap, item_cap, 1024,
-                                ix->dev.row_bytes + (int32_t)ws_row, alloc, stream, &res);
-    if (st == RR_ENOMEM && ws_row > 0) {
-        ws_row = 0;
+    // the float scan's scratch lies in the hash table, which has no other use
+    // here; where there is no room for it the FP64 scan runs, which needs none
+    int64_t ws = nq > 0 ? scan_ws_bytes(ix->dev, nq) : 0;
+    rr_status st = make_results(ix, ix->dev, nq, &sp, true, item_cap, item_cap, std::max<int64_t>(1024, (ws + 7) / 8),
+                                ix->dev.row_bytes, alloc, stream, &res);
+    if (st == RR_ENOMEM && ws > 0) {
+        ws = 0;
         st = make_results(ix, ix->dev, nq, &sp, true, item_cap, item_cap, 1024, ix->dev.row_bytes, alloc,
                           stream, &res);
     }
@@ -1106,15 +1106,20 @@ static rr_status brute_force_once(const rr_index *ix, const void *queries_dev, i
     HIP_TRY_R(launch_fill_u64(sb.counters, CTR_COUNT, 0ull, s));
     HIP_TRY_R(launch_fill_u64(sb.level_cnt, sb.max_levels, 0ull, s));
     HIP_TRY_R(launch_prep_queries(ix->dev, queries_dev, nq, radius, radius_dev, cfg, sb, s));
-    HIP_TRY_R(launch_brute_force(ix->dev, sb.qpad, sb.qth, nq, sb,
-                                 ws_row > 0 ? sb.qpad + nq * ix->dev.row_bytes : nullptr, device_cus(), s));
+    uint8_t *wsp = ws > 0 ? (uint8_t *)sb.hash : nullptr;
+    HIP_TRY_R(launch_brute_force(ix->dev, sb.qpad, sb.qth, nq, sb, wsp, device_cus(), s));
     // the hit count decides whether the capacity sufficed (ground truth is
     // not on a timed path, so this call synchronizes)
-    unsigned long long h = 0;
-    HIP_TRY_R(hipMemcpyAsync(&h, sb.level_cnt, sizeof h, hipMemcpyDeviceToHost, s));
+    unsigned long long h[2] = {0, 0};
+    HIP_TRY_R(hipMemcpyAsync(h, sb.level_cnt, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_TRY_R(hipStreamSynchronize(s));
-    *hits = (int64_t)h;
-    if ((int64_t)h > item_cap) {
+    if (wsp && h[1] > 0) {
+        HIP_TRY_R(launch_brute_force_dense(ix->dev, sb.qpad, sb.qth, nq, sb, wsp, s));
+        HIP_TRY_R(hipMemcpyAsync(h, sb.level_cnt, sizeof h, hipMemcpyDeviceToHost, s));
+        HIP_TRY_R(hipStreamSynchronize(s));
+    }
+    *hits = (int64_t)h[0];
+    if ((int64_t)h[0] > item_cap) {
         rr_results_free(res);
         return RR_OK; // caller retries with the exact capacity
     }
@@ -1297,7 +1302,7 @@ extern "C" rr_status rr_nn_dist(const rr_index *ix, const void *queries_dev, int
     al.stream = stream;
     const size_t qrows = (size_t)nq * ix->dev.row_bytes;
     // the float scan's scratch follows the queries, as in brute_force_once
-    size_t ws = (size_t)nq * scan_ws_row(ix->dev);
+    size_t ws = (size_t)scan_ws_bytes(ix->dev, nq);
     auto rows_end = [&]() { return (qrows + ws + 255) & ~(size_t)255; };
     auto bytes = [&]() { return rows_end() + (size_t)nq * (sizeof(QThresh) + 8) + 512; };
     uint8_t *tmp = (uint8_t *)al.alloc(bytes());

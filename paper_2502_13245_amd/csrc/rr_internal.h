@@ -125,7 +125,7 @@ struct SearchBufs {
     int64_t item_cap = 0;
     unsigned long long *u_key = nullptr; // [item_cap] a level as emitted, before grouping by task
     void *u_dist = nullptr;
-    unsigned long long *level_cnt = nullptr; // [max_levels] items per level (brute force: hits)
+    unsigned long long *level_cnt = nullptr; // [max_levels] items per level (brute force: hits, runs of tiles)
     unsigned long long *level_clock = nullptr; // [1 + 3 * LEVEL_CLOCKS] greedy phase timestamps
     int32_t max_levels = 0;
     unsigned long long *hash = nullptr; // [hash_cap] (task << 32 | id), ~0 = empty
@@ -241,9 +241,12 @@ hipError_t launch_results_copy(int dtype, int precision, const DevIndex &ix, con
                                int64_t capacity = INT64_MAX, bool scan_counts = true);
 size_t results_copy_tmp_bytes(int64_t nq);
 
-// brute force (rr_scan.hip); ws: scan_ws_row(ix) bytes of scratch per query,
-// or null (float data then takes the FP64 scan)
-int64_t scan_ws_row(const DevIndex &ix);
+// brute force (rr_scan.hip); ws: scan_ws_bytes of scratch, or null (float data
+// then takes the FP64 scan).  level_cnt[0] counts the hits, level_cnt[1] what
+// is left to launch_brute_force_dense.
+int64_t scan_ws_bytes(const DevIndex &ix, int64_t nq);
+hipError_t launch_brute_force_dense(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth, int64_t nq,
+                                    SearchBufs &sb, uint8_t *ws, hipStream_t s);
 hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth,
                               int64_t nq, SearchBufs &sb, uint8_t *ws, int num_cus, hipStream_t s);
 // memory-system probe (rr_probe.hip): partial sums written, and the launch

@@ -41,9 +41,12 @@ __device__ __forceinline__ double dbl_unorder(unsigned long long k) {
 }
 
 // rr_scan_f32.hip: whether the split-bfloat16 scan takes this index, and its
-// two scans (ws: scan_ws_row bytes per query)
+// two scans (ws: scan_ws_bytes, 16-byte aligned)
 bool scan_split_ok(const DevIndex &ix);
+// the range scan, but for the tiles that a list in ws names (their count goes to
+// item_cursor[1]); the second call decides those
 hipError_t launch_split_range(const ScanArgs &a, uint8_t *ws, hipStream_t s);
+hipError_t launch_split_range_dense(const ScanArgs &a, uint8_t *ws, hipStream_t s);
 // writes nn_bits (dbl_order of the smallest distance of every query)
 hipError_t launch_split_nn(const ScanArgs &a, uint8_t *ws, hipStream_t s);
 

@@ -630,16 +630,7 @@ hipError_t launch_nn_dist(const DevIndex &ix, const uint8_t *qpad, int64_t nq, d
     return hipGetLastError();
 }
 
-hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth,
-                              int64_t nq, SearchBufs &sb, uint8_t *ws, int num_cus, hipStream_t s) {
-    (void)num_cus;
-    if (nq == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_identity_tasks, dim3((unsigned)std::min<int64_t>((nq + 255) / 256, 4096)),
-                       dim3(256), 0, s, sb.task_q, nq, sb.counters);
-    hipError_t e = launch_fill_u64(sb.task_cnt, nq, 0ull, s);
-    if (e != hipSuccess) return e;
-    e = launch_fill_u64(sb.task_evals, nq, 0ull, s);
-    if (e != hipSuccess) return e;
+static ScanArgs range_args(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth, int64_t nq, SearchBufs &sb) {
     ScanArgs a{};
     a.ix = ix;
     a.qpad = qpad;
@@ -651,6 +642,25 @@ hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QTh
     a.item_cursor = &sb.level_cnt[0];
     a.task_cnt = sb.task_cnt;
     a.overflow = &sb.counters[CTR_OVERFLOW];
+    return a;
+}
+
+hipError_t launch_brute_force_dense(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth, int64_t nq,
+                                    SearchBufs &sb, uint8_t *ws, hipStream_t s) {
+    return launch_split_range_dense(range_args(ix, qpad, qth, nq, sb), ws, s);
+}
+
+hipError_t launch_brute_force(const DevIndex &ix, const uint8_t *qpad, const QThresh *qth,
+                              int64_t nq, SearchBufs &sb, uint8_t *ws, int num_cus, hipStream_t s) {
+    (void)num_cus;
+    if (nq == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_identity_tasks, dim3((unsigned)std::min<int64_t>((nq + 255) / 256, 4096)),
+                       dim3(256), 0, s, sb.task_q, nq, sb.counters);
+    hipError_t e = launch_fill_u64(sb.task_cnt, nq, 0ull, s);
+    if (e != hipSuccess) return e;
+    e = launch_fill_u64(sb.task_evals, nq, 0ull, s);
+    if (e != hipSuccess) return e;
+    const ScanArgs a = range_args(ix, qpad, qth, nq, sb);
     return ws && scan_split_ok(ix) ? launch_split_range(a, ws, s) : launch_scan(a, SCAN_RANGE, s);
 }
 

@@ -8,7 +8,9 @@
 // pair inside the radius can fail; the few pairs that pass are decided, and
 // their distances computed, in FP64 from the float32 rows, chunk by chunk in
 // the order of the graph search's kernels, so a scan and a search report the
-// same bits.
+// same bits.  Where many pairs pass (large radii, values far from the origin
+// or of very different lengths) whole tiles are decided that way
+// (k_split_dense).
 //
 // What bounds it: the float64 products would take 5.4 ms for 2,000 queries x
 // 1M x 96 values at the 70 TFLOP/s that a large FP64 matrix product reaches
@@ -53,9 +55,23 @@ enum { SPLIT_MAX = 0, SPLIT_RANGE = 1, SPLIT_MIN = 2 };
 constexpr int SPLIT_TILE = 64;   // base points per step
 constexpr int SPLIT_Q = 128;     // queries per workgroup
 constexpr int SPLIT_STAGE = 128; // staged candidates per wave
+// A tile of 64 points and a wave's 32 queries with SPLIT_DENSE candidates (of
+// 2,048 pairs) is left to k_split_dense, and so are the tiles that follow it
+// with SPLIT_STAY.  That kernel takes 13 ps a pair of 96 values and 95 ps of 768
+// (a tile 27 and 195 ns); a candidate decided by itself takes 60 to 145 ps and
+// 650 ps, in a wave that its workgroup waits for.  200,000 x 96, 500 queries,
+// a radius that 10% (20%) of the pairs lie in: 6.97 (12.3) ms from 384, 7.16
+// (12.1) from 256, 7.8 (11.1) from 192, 7.9 (10.8) from 128; 50,000 x 768 with
+// 20% 10.8, 9.1, 6.9 and 6.7.
+constexpr int SPLIT_DENSE = 192;
+constexpr int SPLIT_STAY = 128;
 
 struct SplitArgs {
     ScanArgs sc;
+    uint4 *dense;        // [dense_cap] runs of such tiles: 32-query block, first point, end
+    unsigned long long *dense_cnt;
+    int64_t dense_cap;   // 0: none are kept
+    int32_t run_max;     // tiles of a run
     const uint16_t *qs;  // [nq][2][kpad] high and low parts of the queries
     const float *cinit;  // [nq] what the sums start from
     unsigned *best;      // [nq] SPLIT_MAX: ordered bits of the largest sum
@@ -96,9 +112,10 @@ __device__ __forceinline__ void split8(f32x8 x, uint4 &hi, uint4 &lo) {
 // FP64 decision.
 __global__ void k_split_prep(const uint8_t *qpad, const QThresh *qth, int64_t nq, int32_t row_bytes,
                              int32_t d, int32_t kpad, double maxnorm, int ip, uint16_t *qs, float *cinit,
-                             float *slack_out, unsigned *best) {
+                             float *slack_out, unsigned *best, unsigned long long *dense_cnt) {
     const int lane = threadIdx.x & 63;
     const int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (q == 0 && lane == 0) *dense_cnt = 0ull;
     if (q >= nq) return;
     const float *qr = reinterpret_cast<const float *>(qpad + q * row_bytes);
     double n2 = 0.0;
@@ -140,11 +157,38 @@ __global__ void k_split_best(const unsigned *best, const float *slack, int64_t n
     nn_bits[q] = dbl_order(__builtin_huge_val());
 }
 
+// a wave's staged hits to the item arrays, with one cursor atomic, and one
+// count per run of hits of a query
+__device__ __forceinline__ void split_emit(const SplitArgs &a, const uint32_t *st_q, const uint32_t *st_id,
+                                           const double *st_d, int n, int lane) {
+    wave_sync();
+    unsigned long long base = 0;
+    if (lane == 0) base = atomicAdd(a.sc.item_cursor, (unsigned long long)n);
+    base = __shfl(base, 0);
+    for (int i0 = 0; i0 < n; i0 += 64) {
+        const int i = i0 + lane;
+        const int64_t pos = (int64_t)base + i;
+        const bool in = i < n && pos < a.sc.item_cap; // (a prefix of the lanes)
+        const uint32_t q = in ? st_q[i] : ~0u, before = __shfl_up(q, 1);
+        if (in) {
+            a.sc.item_key[pos] = ((unsigned long long)q << 32) | st_id[i];
+            ((double *)a.sc.item_dist)[pos] = st_d[i];
+        }
+        const bool head = in && (lane == 0 || before != q);
+        const unsigned long long hm = __ballot(head), im = __ballot(in); // (by every lane)
+        const unsigned long long later = hm & ~((2ull << lane) - 1ull);
+        const int end = later ? __ffsll((long long)later) - 1 : __popcll(im);
+        if (head) atomicAdd(&a.sc.task_cnt[q], (unsigned long long)(end - lane));
+    }
+    if (lane == 0 && (int64_t)base + n > a.sc.item_cap) atomicOr(a.sc.overflow, 64ull);
+    wave_sync();
+}
+
 // The staged pairs of one wave, decided in FP64: groups of g lanes read a
-// pair's rows, each lane cpl chunks, summed as eval_rows sums them.  Hits are
+// pair's rows, each lane cpl chunks, summed as eval64 sums them.  Hits are
 // compacted in place (a round's reads precede its writes, which land at or
-// below its first entry) and appended to the item arrays with one cursor
-// atomic (SPLIT_RANGE), or lower their query's minimum (SPLIT_MIN).
+// below its first entry) and appended to the item arrays (SPLIT_RANGE), or
+// lower their query's minimum (SPLIT_MIN).
 template <int MODE>
 __device__ __forceinline__ void split_flush(const SplitArgs &a, uint32_t *st_q, uint32_t *st_id,
                                             double *st_d, int n, int lane) {
@@ -152,7 +196,7 @@ __device__ __forceinline__ void split_flush(const SplitArgs &a, uint32_t *st_q, 
     const int g = a.g, cpl = a.cpl, gl = lane & (g - 1), per = 64 / g;
     const bool ip = a.sc.ix.metric == RR_IP;
     const size_t rb = a.sc.ix.row_bytes;
-    int kept = 0;
+    int kept = 0; // (hits)
     for (int e0 = 0; e0 < n; e0 += per) {
         const int e = e0 + lane / g;
         const uint32_t q = st_q[min(e, n - 1)], id = st_id[min(e, n - 1)];
@@ -164,7 +208,10 @@ __device__ __forceinline__ void split_flush(const SplitArgs &a, uint32_t *st_q, 
         if (ip) s = -s;
         const bool mine = gl == 0 && e < n;
         if (MODE == SPLIT_MIN) {
-            if (mine && s <= __builtin_huge_val()) atomicMin(&a.sc.nn_bits[q], dbl_order(s));
+            // (a load first: an atomic for every candidate is 40 to 90 ps of it;
+            // the value only falls, so an old one costs an atomic at most)
+            if (mine && s <= __builtin_huge_val() && dbl_order(s) < a.sc.nn_bits[q])
+                atomicMin(&a.sc.nn_bits[q], dbl_order(s));
         } else {
             const bool hit = mine && s <= a.sc.qth[q].r;
             const unsigned long long hm = __ballot(hit);
@@ -179,21 +226,7 @@ __device__ __forceinline__ void split_flush(const SplitArgs &a, uint32_t *st_q, 
         }
         wave_sync();
     }
-    if (MODE == SPLIT_RANGE && kept > 0) {
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(a.sc.item_cursor, (unsigned long long)kept);
-        base = __shfl(base, 0);
-        for (int i = lane; i < kept; i += 64) {
-            const int64_t pos = (int64_t)base + i;
-            if (pos < a.sc.item_cap) {
-                a.sc.item_key[pos] = ((unsigned long long)st_q[i] << 32) | st_id[i];
-                ((double *)a.sc.item_dist)[pos] = st_d[i];
-                atomicAdd(&a.sc.task_cnt[st_q[i]], 1ull);
-            }
-        }
-        if (lane == 0 && (int64_t)base + kept > a.sc.item_cap) atomicOr(a.sc.overflow, 64ull);
-        wave_sync();
-    }
+    if (MODE == SPLIT_RANGE && kept > 0) split_emit(a, st_q, st_id, st_d, kept, lane);
 }
 
 // KS: 16-value steps held at a time (even); MULTI: rows of more than 16 KS
@@ -268,6 +301,14 @@ __global__ __launch_bounds__(256, 2) void k_scan_split(SplitArgs a) {
         lim[v] = -__builtin_huge_valf();
     }
     int scnt = 0; // staged candidates of this wave (wave-uniform)
+    // the open run of dense tiles (none: run = -1)
+    int64_t run = -1, run_p = 0;
+    int run_n = 0;
+    auto close_run = [&](int64_t end) {
+        if (run >= 0 && lane == 0)
+            a.dense[run] = make_uint4((uint32_t)(q0 / 32), (uint32_t)run_p, (uint32_t)end, 0u);
+        run = -1;
+    };
     f32x16 acc[2];
     load_x(p_begin, 0);
     int buf = 0;
@@ -314,19 +355,56 @@ __global__ __launch_bounds__(256, 2) void k_scan_split(SplitArgs a) {
             buf ^= 1;
         }
         if (!active) continue;
+        if (MODE == SPLIT_MAX) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            if (MODE == SPLIT_MAX) {
+            for (int t = 0; t < 2; ++t)
                 if (pv[t]) {
 #pragma unroll
                     for (int v = 0; v < 16; ++v) lim[v] = fmaxf(lim[v], acc[t][v] - hx[t]);
                 }
-                continue;
-            }
+            continue;
+        }
+        unsigned long long some[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
             float top = acc[t][0];
 #pragma unroll
             for (int v = 1; v < 16; ++v) top = fmaxf(top, acc[t][v]);
-            if (!__ballot(pv[t] && top >= hx[t])) continue;
+            some[t] = __ballot(pv[t] && top >= hx[t]);
+        }
+        // (so many candidates lie on half of the lanes' columns or more, but for
+        // the most uneven tiles)
+        bool dense = false;
+        if (a.dense_cap > 0 && __popcll(some[0]) + __popcll(some[1]) >= 64) {
+            int n = 0;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) n += __popcll(__ballot(pv[t] && acc[t][v] >= hx[t]));
+            dense = n >= (run >= 0 ? SPLIT_STAY : SPLIT_DENSE);
+        }
+        if (dense) {
+            if (run >= 0 && run_n == a.run_max) close_run(p0);
+            if (run < 0) {
+                unsigned long long r = 0;
+                if (lane == 0) r = atomicAdd(a.dense_cnt, 1ull);
+                r = (unsigned long long)uniform64((int64_t)r);
+                dense = (int64_t)r < a.dense_cap; // else the tile is decided like any other
+                if (dense) {
+                    run = (int64_t)r;
+                    run_p = p0;
+                    run_n = 0;
+                }
+            }
+            if (dense) {
+                ++run_n;
+                continue;
+            }
+        }
+        if (run >= 0) close_run(p0);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (!some[t]) continue;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const bool cand = pv[t] && acc[t][v] >= hx[t];
@@ -355,9 +433,196 @@ __global__ __launch_bounds__(256, 2) void k_scan_split(SplitArgs a) {
             const int64_t q = q0 + 8 * (v / 4) + 4 * half + v % 4;
             if (l32 == 0 && q < a.sc.nq) atomicMax(&a.best[q], flt_order(m));
         }
-    } else if (scnt > 0) {
-        split_flush<MODE>(a, st_q, st_id, st_d, scnt, lane);
+    } else {
+        close_run(p_end);
+        if (scnt > 0) split_flush<MODE>(a, st_q, st_id, st_d, scnt, lane);
     }
+}
+
+// A group of chunks is summed (its pairs' sums in `v`): neighbouring groups
+// first, then neighbouring pairs of groups, ...  S[i] holds the last sums of 2^i
+// groups that wait for their neighbours'; group l completes the levels of its
+// trailing ones.  After the last group v holds the whole sums.
+template <int I, int L> __device__ __forceinline__ void dense_merge(double (&S)[L][8], double (&v)[8], int l, int low) {
+    if constexpr (I < L) {
+        if (((I < 3 ? low : l) >> I) & 1) { // low: l's last three bits
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] += S[I][i];
+            dense_merge<I + 1, L>(S, v, l, low);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) S[I][i] = v[i];
+        }
+    }
+}
+
+// The runs of dense tiles, every pair in FP64 from the float32 rows: 2^L groups
+// of cpl chunks a row, a group's chunks in their order and then halves
+// together, which are the sums of eval64 to the last bit.  A workgroup takes a
+// tile of 32 queries and 64 points through LDS, 128 bytes of each row at a time
+// (loaded a step ahead); a lane has 2 queries and 4 points, so that 6 chunks
+// read serve 8 pairs.  Bound by the FP64 vector units: 8 pairs of a chunk are
+// 24 conversions, 32 subtractions and 32 products, 7.3 and 58 ps a pair of 96
+// and 768 values without a wait; it takes 13 and 95 (the FP64 scan: 16 and 145).
+// With 6 chunks read from the L1 cache instead, 27 and 195.  Calls in which
+// every pair passes the filter, FP64 scan / candidates one by one / now:
+// nearest distances of 2,000 queries x 200,000 x 96 6.6 / 34.5 / 6.0 ms, of
+// 2,000 x 50,000 x 768 14.4 / 70.4 / 11.1 ms, of 2,000 x 200,000 x 16 (two passes
+// of the filter are half of it) 1.15 / 31 / 1.57 ms; a radius around half of
+// 500 x 50,000 x 768 pairs 14.3 / 25.7 / 9.3 ms.
+template <int L, bool ONE, bool IP, int MODE>
+__global__ __launch_bounds__(256, L <= 2 && MODE == SPLIT_MIN ? 3 : 2) void k_split_dense(SplitArgs a) {
+    // (ONE: a group is one chunk, and the order of the sums is known while the
+    // loop over a step's chunks is unrolled)
+    constexpr int ROWS = SPLIT_TILE + 32; // points, then queries
+    constexpr int STAGE = MODE == SPLIT_RANGE ? 320 : 1;
+    __shared__ uint4 xt[2][ROWS * 8];
+    __shared__ double sd[4][STAGE];
+    __shared__ uint32_t sq[4][STAGE], si[4][STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int64_t runs = min((int64_t)*a.dense_cnt, a.dense_cap);
+    const size_t rb = a.sc.ix.row_bytes;
+    const int chunks = a.sc.ix.row_bytes / 16, cpl = a.cpl;
+    // (16 lanes that read one chunk column of 16 rows fall on different banks)
+    auto place = [](int row, int c) { return row * 8 + (c ^ ((row >> 1) & 7)); };
+    int buf = 0;
+    for (int64_t it = blockIdx.x; it < runs; it += gridDim.x) {
+        const uint4 r = a.dense[it];
+        const int64_t q0 = (int64_t)r.x * 32, end = r.z;
+        const int ql = wid * 8 + (lane >> 4) * 2, pl = lane & 15; // of the lane, in the tile
+        double lim[2]; // the radius, or the smallest distance so far
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            lim[i] = MODE == SPLIT_RANGE ? a.sc.qth[min(q0 + ql + i, a.sc.nq - 1)].r : __builtin_huge_val();
+        uint4 nx[3];
+        auto load = [&](int64_t p0, int c0) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const int row = (tid + 256 * j) / 8, c = c0 + tid % 8;
+                const uint8_t *x = j < 2 ? a.sc.ix.base + min(p0 + row, a.sc.ix.n - 1) * rb
+                                         : a.sc.qpad + min(q0 + row - SPLIT_TILE, a.sc.nq - 1) * rb;
+                nx[j] = c < chunks ? *reinterpret_cast<const uint4 *>(x + c * 16) : make_uint4(0u, 0u, 0u, 0u);
+            }
+        };
+        load(r.y, 0);
+        int n = 0; // staged hits (wave-uniform)
+        for (int64_t p0 = r.y; p0 < end; p0 += SPLIT_TILE) {
+            double S[L][8], v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = 0.0;
+            int k = 0, l = 0; // chunks of the open group, its number
+            for (int c0 = 0; c0 < chunks; c0 += 8, buf ^= 1) {
+                // (the other buffer is free: every wave that has passed this
+                // step's barrier is done with the step before)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) xt[buf][place((tid + 256 * j) / 8, tid % 8)] = nx[j];
+                __syncthreads();
+                if (c0 + 8 < chunks) load(p0, c0 + 8);
+                else if (p0 + SPLIT_TILE < end) load(p0 + SPLIT_TILE, 0);
+                auto add = [&](int c) __attribute__((always_inline)) {
+                    uint4 y[2], x[4];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) y[i] = xt[buf][place(SPLIT_TILE + ql + i, c)];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[j] = xt[buf][place(16 * j + pl, c)];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            v[4 * i + j] += IP ? chunk_ip<RR_F32>(x[j], y[i]) : chunk_part<RR_F32>(x[j], y[i]);
+                };
+                auto close = [&](int low) __attribute__((always_inline)) {
+                    dense_merge<0, L>(S, v, l, low);
+                    if (++l < (1 << L)) {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) v[i] = 0.0;
+                    }
+                };
+                if constexpr (ONE) {
+#pragma unroll
+                    for (int c = 0; c < (L == 2 ? 4 : 8); ++c) {
+                        add(c);
+                        close(c);
+                    }
+                } else {
+                    const int m = min(8, chunks - c0);
+#pragma unroll 2
+                    for (int c = 0; c < m; ++c) {
+                        add(c);
+                        if (++k == cpl) {
+                            close(l & 7);
+                            k = 0;
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int64_t q = q0 + ql + i;
+                bool hit[4];
+                unsigned long long hm[4];
+                int nh = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double d = IP ? -v[4 * i + j] : v[4 * i + j];
+                    hit[j] = q < a.sc.nq && p0 + 16 * j + pl < end && (MODE == SPLIT_MIN ? d < lim[i] : d <= lim[i]);
+                    if (MODE == SPLIT_MIN) {
+                        lim[i] = hit[j] ? d : lim[i];
+                    } else {
+                        hm[j] = __ballot(hit[j]);
+                        nh += __popcll(hm[j]);
+                    }
+                }
+                if (MODE == SPLIT_MIN || nh == 0) continue;
+                if (n + nh > STAGE) {
+                    split_emit(a, sq[wid], si[wid], sd[wid], n, lane);
+                    n = 0;
+                }
+                // the hits of a query (16 lanes, four points each) one after the other
+                const int sh = lane & 48;
+                int o = n;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    o += __popcll(hm[j] & ((1ull << sh) - 1ull)) + __popc((unsigned)(hm[j] >> sh) & ((1u << pl) - 1u));
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (hit[j]) {
+                        sq[wid][o] = (uint32_t)q;
+                        si[wid][o] = (uint32_t)(p0 + 16 * j + pl);
+                        sd[wid][o] = IP ? -v[4 * i + j] : v[4 * i + j];
+                        ++o;
+                    }
+                n += nh;
+            }
+        }
+        if (MODE == SPLIT_MIN) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                double m = lim[i];
+                for (int o = 1; o < 16; o <<= 1) m = fmin(m, __shfl_xor(m, o));
+                if (pl == 0 && q0 + ql + i < a.sc.nq) atomicMin(&a.sc.nn_bits[q0 + ql + i], dbl_order(m));
+            }
+        } else if (n > 0) {
+            split_emit(a, sq[wid], si[wid], sd[wid], n, lane);
+        }
+    }
+}
+
+template <bool IP, int MODE> static hipError_t run_dense(const SplitArgs &a, hipStream_t s) {
+    const dim3 grid(2 * device_cus()), block(256);
+#define RR_DENSE(L)                                                                           \
+    if (a.g == (1 << L)) {                                                                    \
+        if (a.cpl == 1) hipLaunchKernelGGL((k_split_dense<L, true, IP, MODE>), grid, block, 0, s, a); \
+        else hipLaunchKernelGGL((k_split_dense<L, false, IP, MODE>), grid, block, 0, s, a);    \
+        return hipGetLastError();                                                             \
+    }
+    RR_DENSE(2) RR_DENSE(3) RR_DENSE(4) RR_DENSE(5) RR_DENSE(6)
+#undef RR_DENSE
+    return hipErrorInvalidValue;
+}
+template <int MODE> static hipError_t dispatch_dense(const SplitArgs &a, hipStream_t s) {
+    if (a.dense_cap == 0) return hipSuccess;
+    return a.sc.ix.metric == RR_IP ? run_dense<true, MODE>(a, s) : run_dense<false, MODE>(a, s);
 }
 
 // float32 squares of the base and of the products must be normal numbers:
@@ -372,19 +637,40 @@ static int32_t split_kpad(int32_t d) {
     return (d + k - 1) / k * k;
 }
 
-// split queries, then the threshold term, the slack and the best sum of
-// every query; per query a multiple of 16 bytes
-int64_t scan_ws_row(const DevIndex &ix) {
-    return scan_split_ok(ix) ? (int64_t)split_kpad(ix.d) * 4 + 16 : 0;
+// Runs of dense tiles that are kept: enough for every tile of up to 65,536, and
+// beyond that for runs of 8 tiles with gaps between them; at 1M runs (16 MB)
+// the runs get longer.  Scans of fewer pairs than SPLIT_FEW keep none: at most
+// 43 us of single decisions, and one launch less.
+constexpr int64_t SPLIT_FEW = 65536;
+struct DenseRoom {
+    int64_t cap;
+    int32_t run_max;
+};
+static DenseRoom dense_room(int64_t n, int64_t nq) {
+    if (n * nq < SPLIT_FEW) return {0, 1};
+    const int64_t tiles = (n + SPLIT_TILE - 1) / SPLIT_TILE * ((nq + 31) / 32);
+    const int64_t cap = std::min<int64_t>({tiles, std::max<int64_t>(65536, tiles / 4), 1 << 20});
+    return {cap, (int32_t)std::max<int64_t>(8, 4 * tiles / cap)};
+}
+
+// the runs and their count, then split queries, the threshold term, the slack
+// and the best sum of every query
+int64_t scan_ws_bytes(const DevIndex &ix, int64_t nq) {
+    return scan_split_ok(ix) ? 16 + 16 * dense_room(ix.n, nq).cap + nq * ((int64_t)split_kpad(ix.d) * 4 + 12) : 0;
 }
 
 struct SplitWs {
+    unsigned long long *dense_cnt;
+    uint4 *dense;
     uint16_t *qs;
     float *cinit, *slack;
     unsigned *best;
 };
 static SplitWs split_ws(const DevIndex &ix, int64_t nq, uint8_t *ws) {
     SplitWs w;
+    w.dense_cnt = reinterpret_cast<unsigned long long *>(ws);
+    w.dense = reinterpret_cast<uint4 *>(ws + 16);
+    ws += 16 + 16 * dense_room(ix.n, nq).cap;
     w.qs = reinterpret_cast<uint16_t *>(ws);
     w.cinit = reinterpret_cast<float *>(ws + nq * (int64_t)split_kpad(ix.d) * 4);
     w.slack = w.cinit + nq;
@@ -412,9 +698,15 @@ template <int MODE> static hipError_t dispatch_split(SplitArgs &a, hipStream_t s
     }
 }
 
-static hipError_t split_setup(const ScanArgs &sc, uint8_t *ws, SplitArgs &a, SplitWs &w, hipStream_t s) {
-    w = split_ws(sc.ix, sc.nq, ws);
+static SplitWs split_args(const ScanArgs &sc, uint8_t *ws, SplitArgs &a) {
+    const SplitWs w = split_ws(sc.ix, sc.nq, ws);
     a.sc = sc;
+    a.dense = w.dense;
+    // (a range scan's count lies behind its hit count: the caller copies both)
+    a.dense_cnt = sc.item_cursor ? sc.item_cursor + 1 : w.dense_cnt;
+    const DenseRoom room = dense_room(sc.ix.n, sc.nq);
+    a.dense_cap = room.cap;
+    a.run_max = room.run_max;
     a.qs = w.qs;
     a.cinit = w.cinit;
     a.best = w.best;
@@ -425,9 +717,14 @@ static hipError_t split_setup(const ScanArgs &sc, uint8_t *ws, SplitArgs &a, Spl
     a.sc.chunk = sp.chunk * SPLIT_TILE;
     a.sc.xcds = sp.xcds;
     a.groups = sp.groups(a.sc.qblocks);
+    return w;
+}
+
+static hipError_t split_setup(const ScanArgs &sc, uint8_t *ws, SplitArgs &a, SplitWs &w, hipStream_t s) {
+    w = split_args(sc, ws, a);
     hipLaunchKernelGGL(k_split_prep, dim3((unsigned)((sc.nq + 3) / 4)), dim3(256), 0, s, sc.qpad, sc.qth, sc.nq,
                        sc.ix.row_bytes, sc.ix.d, a.kpad, (double)sc.ix.max_norm, (int)(sc.ix.metric == RR_IP),
-                       w.qs, w.cinit, w.slack, w.best);
+                       w.qs, w.cinit, w.slack, w.best, a.dense_cnt);
     return hipGetLastError();
 }
 
@@ -436,6 +733,12 @@ hipError_t launch_split_range(const ScanArgs &sc, uint8_t *ws, hipStream_t s) {
     SplitWs w;
     const hipError_t e = split_setup(sc, ws, a, w, s);
     return e != hipSuccess ? e : dispatch_split<SPLIT_RANGE>(a, s);
+}
+
+hipError_t launch_split_range_dense(const ScanArgs &sc, uint8_t *ws, hipStream_t s) {
+    SplitArgs a;
+    split_args(sc, ws, a);
+    return dispatch_dense<SPLIT_RANGE>(a, s);
 }
 
 // Two passes: the largest approximate sum of every query, then the pairs
@@ -454,7 +757,8 @@ hipError_t launch_split_nn(const ScanArgs &sc, uint8_t *ws, hipStream_t s) {
     hipLaunchKernelGGL(k_split_best, dim3((unsigned)((sc.nq + 255) / 256)), dim3(256), 0, s, w.best, w.slack,
                        sc.nq, w.cinit, sc.nn_bits);
     e = hipGetLastError();
-    return e != hipSuccess ? e : dispatch_split<SPLIT_MIN>(a, s);
+    if (e == hipSuccess) e = dispatch_split<SPLIT_MIN>(a, s);
+    return e != hipSuccess ? e : dispatch_dense<SPLIT_MIN>(a, s);
 }
 
 } // namespace rr
