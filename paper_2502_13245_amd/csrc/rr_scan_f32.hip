@@ -114,34 +114,35 @@ __global__ void k_split_prep(const uint8_t *qpad, const QThresh *qth, int64_t nq
                              int32_t d, int32_t kpad, double maxnorm, int ip, uint16_t *qs, float *cinit,
                              float *slack_out, unsigned *best, unsigned long long *dense_cnt) {
     const int lane = threadIdx.x & 63;
-    const int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (q == 0 && lane == 0) *dense_cnt = 0ull;
-    if (q >= nq) return;
-    const float *qr = reinterpret_cast<const float *>(qpad + q * row_bytes);
-    double n2 = 0.0;
-    for (int i = lane; i < d; i += 64) n2 = fma((double)qr[i], (double)qr[i], n2);
-    for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
-    const bool ok = n2 <= 1e34;
-    const double qn = sqrt(n2), m = maxnorm * (1.0 + 1e-6);
-    const double acc = (double)(3 * kpad + 16) * 0x1p-22;
-    const double r = qth ? qth[q].r : 0.0;
-    double slack = (3.2 * 0x1p-18 + acc) * qn * m + acc * 0.5 * (n2 + m * m + (qth ? fabs(r) : qn * m)) +
-                   (qn + m) * (double)kpad * 0x1p-120 + 1e-30;
-    if (!ok) slack = __builtin_huge_val();
-    uint4 *hi = reinterpret_cast<uint4 *>(qs + (size_t)q * 2 * kpad), *lo = hi + kpad / 8;
-    const int cols = row_bytes / 4;
-    for (int c = lane; c < kpad / 8; c += 64) {
-        f32x8 x = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (ok && c * 8 < cols) x = *reinterpret_cast<const f32x8 *>(qr + c * 8);
-        uint4 h, l;
-        split8(x, h, l);
-        hi[c] = h;
-        lo[c] = l;
-    }
-    if (lane == 0) {
-        cinit[q] = ok ? __double2float_ru((ip ? r : 0.5 * (r - n2)) + slack) : __builtin_huge_valf();
-        slack_out[q] = __double2float_ru(slack);
-        best[q] = 0u; // below the ordered bits of every sum
+    const int64_t w0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (w0 == 0 && lane == 0) *dense_cnt = 0ull;
+    for (int64_t q = w0; q < nq; q += (int64_t)gridDim.x * (blockDim.x >> 6)) {
+        const float *qr = reinterpret_cast<const float *>(qpad + q * row_bytes);
+        double n2 = 0.0;
+        for (int i = lane; i < d; i += 64) n2 = fma((double)qr[i], (double)qr[i], n2);
+        for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+        const bool ok = n2 <= 1e34;
+        const double qn = sqrt(n2), m = maxnorm * (1.0 + 1e-6);
+        const double acc = (double)(3 * kpad + 16) * 0x1p-22;
+        const double r = qth ? qth[q].r : 0.0;
+        double slack = (3.2 * 0x1p-18 + acc) * qn * m + acc * 0.5 * (n2 + m * m + (qth ? fabs(r) : qn * m)) +
+                       (qn + m) * (double)kpad * 0x1p-120 + 1e-30;
+        if (!ok) slack = __builtin_huge_val();
+        uint4 *hi = reinterpret_cast<uint4 *>(qs + (size_t)q * 2 * kpad), *lo = hi + kpad / 8;
+        const int cols = row_bytes / 4;
+        for (int c = lane; c < kpad / 8; c += 64) {
+            f32x8 x = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (ok && c * 8 < cols) x = *reinterpret_cast<const f32x8 *>(qr + c * 8);
+            uint4 h, l;
+            split8(x, h, l);
+            hi[c] = h;
+            lo[c] = l;
+        }
+        if (lane == 0) {
+            cinit[q] = ok ? __double2float_ru((ip ? r : 0.5 * (r - n2)) + slack) : __builtin_huge_valf();
+            slack_out[q] = __double2float_ru(slack);
+            best[q] = 0u; // below the ordered bits of every sum
+        }
     }
 }
 
@@ -642,6 +643,9 @@ static int32_t split_kpad(int32_t d) {
 // the runs get longer.  Scans of fewer pairs than SPLIT_FEW keep none: at most
 // 43 us of single decisions, and one launch less.
 constexpr int64_t SPLIT_FEW = 65536;
+// More queries take the FP64 scan: a launch holds less than 2^32 threads, and 8
+// chunks of the base for each 128 of these are 2^31
+constexpr int64_t SPLIT_MOST = 1ll << 27;
 struct DenseRoom {
     int64_t cap;
     int32_t run_max;
@@ -656,7 +660,7 @@ static DenseRoom dense_room(int64_t n, int64_t nq) {
 // the runs and their count, then split queries, the threshold term, the slack
 // and the best sum of every query
 int64_t scan_ws_bytes(const DevIndex &ix, int64_t nq) {
-    return scan_split_ok(ix) ? 16 + 16 * dense_room(ix.n, nq).cap + nq * ((int64_t)split_kpad(ix.d) * 4 + 12) : 0;
+    return scan_split_ok(ix) && nq <= SPLIT_MOST ? 16 + 16 * dense_room(ix.n, nq).cap + nq * ((int64_t)split_kpad(ix.d) * 4 + 12) : 0;
 }
 
 struct SplitWs {
@@ -722,7 +726,7 @@ static SplitWs split_args(const ScanArgs &sc, uint8_t *ws, SplitArgs &a) {
 
 static hipError_t split_setup(const ScanArgs &sc, uint8_t *ws, SplitArgs &a, SplitWs &w, hipStream_t s) {
     w = split_args(sc, ws, a);
-    hipLaunchKernelGGL(k_split_prep, dim3((unsigned)((sc.nq + 3) / 4)), dim3(256), 0, s, sc.qpad, sc.qth, sc.nq,
+    hipLaunchKernelGGL(k_split_prep, dim3((unsigned)std::min<int64_t>((sc.nq + 3) / 4, 1 << 20)), dim3(256), 0, s, sc.qpad, sc.qth, sc.nq,
                        sc.ix.row_bytes, sc.ix.d, a.kpad, (double)sc.ix.max_norm, (int)(sc.ix.metric == RR_IP),
                        w.qs, w.cinit, w.slack, w.best, a.dense_cnt);
     return hipGetLastError();
