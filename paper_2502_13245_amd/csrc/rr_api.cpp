@@ -649,7 +649,7 @@ static BufLayout layout_bufs(const rr_index *ix, int64_t nq, bool with_greedy, i
         L.sid = c.take<int32_t>(item_cap);
         L.sd = c.take<uint8_t>(item_cap * dsz);
         L.tp = c.take<unsigned long long>(nq);
-        L.lc = c.take<unsigned long long>(1 + 3 * LEVEL_CLOCKS);
+        L.lc = c.take<unsigned long long>(CLOCK_COUNT);
         L.bm = c.take<uint32_t>(bm_tasks * L.bm_words);
         L.uk = c.take<unsigned long long>(item_cap);
         L.ud = c.take<uint8_t>(item_cap * dsz);
@@ -1404,7 +1404,7 @@ extern "C" rr_status rr_results_level_profile(const rr_results *res, int32_t max
     unsigned long long ctr[CTR_COUNT];
     HIP_TRY(hipMemcpy(ctr, res->sb.counters, sizeof ctr, hipMemcpyDeviceToHost));
     const int32_t lv = (int32_t)std::min<unsigned long long>(ctr[CTR_LEVELS], LEVEL_CLOCKS);
-    std::vector<unsigned long long> clk(1 + 3 * LEVEL_CLOCKS), lc((size_t)std::max(lv, 1));
+    std::vector<unsigned long long> clk(CLOCK_COUNT), lc((size_t)std::max(lv, 1));
     HIP_TRY(hipMemcpy(clk.data(), res->sb.level_clock, clk.size() * sizeof(unsigned long long),
                       hipMemcpyDeviceToHost));
     if (lv > 0)
@@ -1419,10 +1419,10 @@ extern "C" rr_status rr_results_level_profile(const rr_results *res, int32_t max
     for (int32_t l = 0; l < n; ++l) {
         const unsigned long long a = clk[1 + 3 * l], c = clk[3 + 3 * l];
         const bool local = l == 1 && res->sb.local_grid > 0;
-        const unsigned long long b = local ? a : prev, e = local ? clk[0] : a; // of the expansion
+        const unsigned long long b = local ? clk[LOCAL_CLOCK] : prev, e = local ? clk[0] : a; // of the expansion
         if (items) items[l] = (int64_t)lc[l];
         // (a stamp of 0: the level kernel had nothing to expand there)
-        if (expand_ms) expand_ms[l] = a && e >= b ? (double)(e - b) * ms_per_tick : 0.0;
+        if (expand_ms) expand_ms[l] = e >= b ? (double)(e - b) * ms_per_tick : 0.0;
         if (regroup_ms) regroup_ms[l] = !local && c && c >= a ? (double)(c - a) * ms_per_tick : 0.0;
         if (!local && a) prev = c ? c : a;
     }

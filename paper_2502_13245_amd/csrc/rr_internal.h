@@ -152,10 +152,10 @@ struct SearchBufs {
 // greedy levels whose phase boundaries are timestamped (wall clock): the
 // level kernel's start, then per level the ends of expansion, segment scan,
 // regroup.  Where the task-local kernel runs, level 1 is its own (the points it
-// found): the level's first stamp is that kernel's start, and it ends before
-// the level kernel starts.
+// found), from its start, the last stamp, to the level kernel's.
 constexpr int LEVEL_CLOCKS = 64;
-constexpr int LOCAL_CLOCK = 1 + 3 * 1;
+constexpr int LOCAL_CLOCK = 1 + 3 * LEVEL_CLOCKS;
+constexpr int CLOCK_COUNT = LOCAL_CLOCK + 1;
 
 // bits of counters[CTR_OVERFLOW]: 1 beam results beyond the arena, 2 / 4
 // greedy items beyond item_cap, 8 the (task, id) set full, 16 too many

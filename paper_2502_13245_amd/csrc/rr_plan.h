@@ -46,34 +46,36 @@ constexpr int LOCAL_LIST = 8192;  // found points a workgroup can hold at most
 constexpr int LOCAL_LEAST = local_margin(LOCAL_WAVES, LOCAL_SEEDS) + 256;
 
 // How the dense scans split the base: `chunk` tiles a workgroup, and workgroup
-// lin takes the chunk lin % xcds + xcds * (lin / xcds / qblocks) for the query
-// block lin / xcds % qblocks.  Workgroups are dealt to the 8 XCDs in turn, so
-// with xcds = 8 all the query blocks of a chunk meet in one L2, and an XCD's
+// lin takes the chunk lin % x + x (lin / x / qblocks) for the query block
+// lin / x % qblocks, x = 2^xcd_bits.  Workgroups are dealt to the 8 XCDs in turn,
+// so with x = 8 all the query blocks of a chunk meet in one L2, and an XCD's
 // share is its ceil(chunks / 8) chunks, however many query blocks there are.
-// About SCAN_GROUPS workgroups, of the splits into multiples of 8 the one
+// About SCAN_GROUPS workgroups, or of the splits into multiples of 8 the one
 // with the smallest share; where even that is a twelfth or more above the mean
 // (a base of few tiles, which any L2 holds), workgroups go to the XCDs as they
 // come.
 constexpr int64_t SCAN_GROUPS = 4096; // several times what is resident
 struct ScanSplit {
     int64_t chunk, chunks; // tiles a workgroup, chunks
-    int32_t xcds;
-    constexpr int64_t groups(int64_t qblocks) const { return qblocks * ((chunks + xcds - 1) / xcds * xcds); }
+    int32_t xcd_bits;
+    constexpr int64_t groups(int64_t qblocks) const {
+        return qblocks * ((chunks + (1 << xcd_bits) - 1) >> xcd_bits << xcd_bits);
+    }
 };
 constexpr ScanSplit scan_split(int64_t tiles, int64_t qblocks) {
     const int64_t want = SCAN_GROUPS / qblocks > 1 ? SCAN_GROUPS / qblocks : 1;
-    int64_t best = -1, chunk = 1;
+    int64_t chunk = (tiles + want - 1) / want, best = ((tiles + chunk - 1) / chunk + 7) / 8 * chunk;
     for (int64_t p = (want + 7) / 8 * 8; p >= 8; p -= 8) {
         const int64_t c = (tiles + p - 1) / p, share = ((tiles + c - 1) / c + 7) / 8 * c;
         // (not for the sake of 3%: fewer and longer chunks end less evenly)
-        if (best < 0 || share * 33 < best * 32) {
+        if (share * 33 < best * 32) {
             best = share;
             chunk = c;
         }
     }
-    if (best * 8 * 12 < tiles * 13) return {chunk, (tiles + chunk - 1) / chunk, 8};
+    if (best * 8 * 12 < tiles * 13) return {chunk, (tiles + chunk - 1) / chunk, 3};
     chunk = (tiles + want - 1) / want;
-    return {chunk, (tiles + chunk - 1) / chunk, 1};
+    return {chunk, (tiles + chunk - 1) / chunk, 0};
 }
 
 } // namespace rr

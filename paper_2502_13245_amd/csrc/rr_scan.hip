@@ -254,12 +254,12 @@ __global__ __launch_bounds__(256, range_waves(KS)) void k_scan_range(ScanArgs a)
     constexpr int ROWS = TILE / PASS, COLS = CPR / TPR; // rows and chunks of a thread per step
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
-    const int64_t lin = blockIdx.x; // (scan_split)
+    const ScanPlace at = scan_place(a);
     // up to QT * 32 queries: every wave takes them all and a fourth of the points
     const bool few = a.nq <= QT * 32;
-    const int64_t q0 = few ? 0 : (((lin / a.xcds) % a.qblocks) * 4 + wid) * (QT * 32);
+    const int64_t q0 = few ? 0 : ((int64_t)at.qblock * 4 + wid) * (QT * 32);
     const int sub0 = few ? wid * 32 : 0, sub_step = few ? 128 : 32;
-    const int64_t p_begin = (lin % a.xcds + a.xcds * (lin / a.xcds / a.qblocks)) * a.chunk;
+    const int64_t p_begin = at.chunk * a.chunk;
     const int64_t p_end = min(a.ix.n, p_begin + a.chunk);
     if (p_begin >= p_end) return;
     const bool active = q0 < a.nq; // waves without queries only help to load
@@ -570,7 +570,7 @@ static hipError_t launch_scan(const ScanArgs &a0, int mode, hipStream_t s) {
         const int tile = range_tile(2 * ks);
         const ScanSplit sp = scan_split((a.ix.n + tile - 1) / tile, qblocks);
         a.chunk = sp.chunk * tile;
-        a.xcds = sp.xcds;
+        a.xcd_bits = sp.xcd_bits;
         const dim3 grid((unsigned)sp.groups(qblocks));
 #define RR_SCAN_KS(K)                                                                         \
     if (ks == K) {                                                                            \

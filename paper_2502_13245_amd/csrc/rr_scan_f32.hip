@@ -243,10 +243,9 @@ __global__ __launch_bounds__(256, 2) void k_scan_split(SplitArgs a) {
     double *st_d = reinterpret_cast<double *>(smem + 4 * PART * 16) + wid * SPLIT_STAGE;
     uint32_t *st_q = reinterpret_cast<uint32_t *>(smem + 4 * PART * 16 + 4 * SPLIT_STAGE * 8) + wid * 2 * SPLIT_STAGE;
     uint32_t *st_id = st_q + SPLIT_STAGE;
-    const int64_t lin = blockIdx.x; // (scan_split)
-    const int64_t pb = lin % a.sc.xcds + a.sc.xcds * (lin / a.sc.xcds / a.sc.qblocks);
-    const int64_t q0 = ((lin / a.sc.xcds) % a.sc.qblocks) * SPLIT_Q + wid * 32;
-    const int64_t p_begin = pb * a.sc.chunk, p_end = min(a.sc.ix.n, p_begin + a.sc.chunk);
+    const ScanPlace at = scan_place(a.sc);
+    const int64_t q0 = (int64_t)at.qblock * SPLIT_Q + wid * 32;
+    const int64_t p_begin = at.chunk * a.sc.chunk, p_end = min(a.sc.ix.n, p_begin + a.sc.chunk);
     if (p_begin >= p_end) return;
     const bool active = q0 < a.sc.nq; // waves without queries only help to load
     const bool ip = a.sc.ix.metric == RR_IP;
@@ -719,7 +718,7 @@ static SplitWs split_args(const ScanArgs &sc, uint8_t *ws, SplitArgs &a) {
     a.sc.qblocks = (int32_t)((sc.nq + SPLIT_Q - 1) / SPLIT_Q);
     const ScanSplit sp = scan_split((sc.ix.n + SPLIT_TILE - 1) / SPLIT_TILE, a.sc.qblocks);
     a.sc.chunk = sp.chunk * SPLIT_TILE;
-    a.sc.xcds = sp.xcds;
+    a.sc.xcd_bits = sp.xcd_bits;
     a.groups = sp.groups(a.sc.qblocks);
     return w;
 }

@@ -1980,7 +1980,7 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
     };
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < 1 + 3 * LEVEL_CLOCKS; i += blockDim.x)
-            if (i != LOCAL_CLOCK || a.sb.local_grid == 0) a.sb.level_clock[i] = i == 0 ? wall_clock64() : 0ull;
+            a.sb.level_clock[i] = i == 0 ? wall_clock64() : 0ull;
     int64_t base = 0;
     int lvl = 0;
     bool grouped = true;

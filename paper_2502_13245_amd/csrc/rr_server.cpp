@@ -271,7 +271,7 @@ int64_t server_bytes(int64_t n, int64_t S, int64_t b, bool greedy, int64_t resul
         add((S + 1) * 8 + S * 8 * 2);    // segment offsets, cursors, previous counts
         add(c.item_cap * (4 + dsz));     // segment ids and distances
         add(S * 8);                      // adjacency entries per task
-        add((1 + 3 * LEVEL_CLOCKS) * 8);
+        add(CLOCK_COUNT * 8);
         add(bitmap_tasks(n, S) * bitmap_words(n) * 4);
     }
     // server buffers: state, stored beams, qlist, staging

@@ -123,13 +123,13 @@ static long scan() {
         for (long qb : {1l, 2l, 3l, 20l, 79l, 98l, 205l, 313l, 391l, 400l, 586l, 800l, 1954l, 7813l}) {
             const ScanSplit s = scan_split(t, qb);
             ++seen;
-            EXPECT(s.chunk >= 1 && s.chunks * s.chunk >= t && (s.chunks - 1) * s.chunk < t && (s.xcds == 1 || s.xcds == 8),
+            EXPECT(s.chunk >= 1 && s.chunks * s.chunk >= t && (s.chunks - 1) * s.chunk < t && (s.xcd_bits == 0 || s.xcd_bits == 3),
                    "%ld tiles, %ld query blocks: chunks %ld of %ld\n", t, qb, (long)s.chunks, (long)s.chunk);
             double load[8] = {0}, most = 0, all = 0;
             std::vector<char> taken;
             if (t * qb < 200000) taken.assign(t * qb, 0);
             for (long lin = 0; lin < s.groups(qb); ++lin) {
-                const long p = lin % s.xcds + s.xcds * (lin / s.xcds / qb), q = lin / s.xcds % qb;
+                const long x = 1l << s.xcd_bits, p = lin % x + x * (lin / x / qb), q = lin / x % qb;
                 const long t0 = p * s.chunk, t1 = std::min<long>(t, t0 + s.chunk);
                 for (long k = t0; k < t1 && !taken.empty(); ++k) ++taken[k * qb + q];
                 if (t1 > t0) load[lin % 8] += t1 - t0;
