@@ -140,6 +140,7 @@ struct SearchBufs {
     // the greedy phase starts with the task-local kernel: its workgroups (0:
     // it is not run) and the found points each may hold
     int32_t local_grid = 0, local_cap = 0;
+    bool local_full = false; // its workgroups fill the GPU
     int64_t *seg_off = nullptr;   // [nq + 1] per-task segment offsets
     unsigned long long *seg_cur = nullptr;   // [nq]
     int64_t *task_out = nullptr;  // [nq] arena offset of each task's sorted list (finalization); before

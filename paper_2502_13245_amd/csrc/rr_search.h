@@ -1736,10 +1736,14 @@ __device__ __forceinline__ void decide64(const DevIndex &ix, const QueryRegs<DTY
 // greedy phase: Algorithm 2 for all tasks at once, level-synchronous
 // --------------------------------------------------------------------------
 
+struct LocalBusy {
+    int low, high; // of local_busy
+};
 struct GreedyArgs {
     DevIndex ix;
     SearchCfg cfg;
     SearchBufs sb;
+    LocalBusy busy; // task-local kernel
 };
 
 // Work layout.  The items of one level are grouped by task: level 0 is
@@ -2332,11 +2336,11 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
 // ticket is ahead of the list waits until the point is there or every point
 // taken has been finished.
 //
-// A large ball would keep one workgroup busy while the others are idle, so a
-// task is handed on when most workgroups are out of tasks and its backlog is
-// long, or when its list is full: the bitmap goes to memory (or its ids to the
-// hash table) and the unexpanded points to the level kernel, which spreads
-// them over the GPU.
+// A large ball would keep one workgroup busy while the rest of the GPU is idle,
+// so a task is handed on when few workgroups are busy (local_busy) and its
+// backlog is long, or when its list is full: the bitmap goes to memory (or its
+// ids to the hash table) and the unexpanded points to the level kernel, which
+// spreads them over the GPU.
 //
 // What bounds it: a wave's chain of two reads (adjacency row, base rows) per
 // point, with 8 to 16 waves a CU.  The level kernel alone spends most of its
@@ -2346,9 +2350,9 @@ __global__ __launch_bounds__((greedy_waves<DTYPE, CPL>() * 64)) void k_greedy(Gr
 // 156K points, lists up to 1.4K 0.67 -> 0.26 ms; 1M x 96 bfloat16 pass, 3.6M
 // points 13.1 -> 6.0 ms; 100K x 768 8-bit pass, 45K points 1.16 -> 0.56 ms.
 // Handing on at a backlog of 384 or 1,024 points took 1 and 4% longer on the
-// first, at an idle half or quarter of the workgroups 5 and 9%.
-constexpr int LOCAL_IDLE = 6;        // eighths of the workgroups out of tasks, and
+// first, with half or three quarters of the workgroups still busy 5 and 9%.
 constexpr int LOCAL_BACKLOG = 192;   // points waiting, from which the level kernel is worth its start
+constexpr int LOCAL_WAIT = 512;      // the same while more workgroups are busy (integer data)
 
 // Whether the task-local kernel runs, with how many workgroups and how long a
 // list each (a list's distances lie in the finalization's item_cap entries,
@@ -2365,7 +2369,23 @@ inline void plan_local(SearchBufs &sb, int64_t n, int64_t nq, int num_cus) {
     const int64_t list = std::min<int64_t>(LOCAL_LIST, (lds / per_cu - fix) / 4);
     sb.bm_words = words;
     sb.local_grid = (int32_t)grid;
+    sb.local_full = grid == per_cu * num_cus;
     sb.local_cap = (int32_t)(std::min<int64_t>(list, sb.item_cap / grid) & ~3ll);
+}
+
+// Workgroups still busy at which tasks are handed on, from a backlog of
+// LOCAL_BACKLOG and of LOCAL_WAIT points.  With a workgroup for all that the GPU
+// holds: a quarter of them.  With fewer tasks than that the level kernel's own
+// time, 100 us and more, has to be gained on them alone: a workgroup expands 2
+// to 6 points a us on float data, where it pays for up to a quarter of the CUs,
+// and 8 on integer data, where it does for a few.  Calls of 12 queries with
+// 1,500 and 4,000 results each, level kernel alone / handed on when three
+// quarters of these 12 are done / now: 1M x 128 uint8 544 / 381 / 498 and 738 /
+// 661 / 657 us, 200K x 96 bfloat16 pass 537 / 578 / 438 and 675 / 1,253 / 534,
+// 100K x 768 8-bit pass 1,094 / 1,241 / 554 and 1,547 / 2,405 / 680.
+inline LocalBusy local_busy(bool full, int grid, int num_cus, bool integer) {
+    if (full) return {grid / 4, grid / 4};
+    return integer ? LocalBusy{num_cus / 64, num_cus / 16} : LocalBusy{num_cus / 4, num_cus / 4};
 }
 
 struct LocalTask {
@@ -2406,7 +2426,6 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
     O *const idist = (O *)a.sb.item_dist;
     O *const sc = (O *)a.sb.seg_dists + (int64_t)blockIdx.x * cap; // the list's distances
     unsigned long long *const queue = &a.sb.counters[CTR_LOCAL_QUEUE];
-    const int64_t idle = (int64_t)gridDim.x * LOCAL_IDLE / 8;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.sb.level_clock[LOCAL_CLOCK] = wall_clock64();
 
     for (;;) {
@@ -2478,11 +2497,13 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
                 }
                 p = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
                 if (p == RR_EMPTY32) break;
-                // now and then: how many workgroups are out of tasks?  (each of
-                // them has taken one ticket past the end)
-                if ((k0 & 31) == 0 && *v_tail - k0 > LOCAL_BACKLOG &&
-                    (int64_t)__hip_atomic_load(queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= ntasks + idle) {
-                    if (lane == 0) *v_stop = 1;
+                // now and then: how many workgroups are busy?  (the others have
+                // taken one ticket past the end each)
+                const int backlog = *v_tail - k0;
+                if ((k0 & 31) == 0 && backlog > LOCAL_BACKLOG) {
+                    const int64_t given = (int64_t)__hip_atomic_load(queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int64_t busy = gridDim.x - max((int64_t)0, given - ntasks);
+                    if (busy <= (backlog > LOCAL_WAIT ? a.busy.high : a.busy.low) && lane == 0) *v_stop = 1;
                 }
             }
             const int32_t f = np == p ? nf : row(p);
@@ -2672,6 +2693,7 @@ static hipError_t run_greedy(const DevIndex &ix, const SearchCfg &cfg, SearchBuf
         if (e != hipSuccess) return e;
         if (n < 1) return hipErrorInvalidConfiguration;
         const int lg = (int)std::min<int64_t>(sb.local_grid, (int64_t)n * num_cus);
+        a.busy = local_busy(sb.local_full, lg, num_cus, !dfloat(DTYPE));
         hipLaunchKernelGGL(lk, dim3(lg), dim3(LW * 64), lsm, s, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
