@@ -42,7 +42,7 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("rr_search.h", "rr_inst.hip", "rr_kernels.hip", "rr_internal.h")
+KERNEL_SOURCES = ("rr_search.h", "rr_inst.hip", "rr_kernels.hip", "rr_internal.h", "rr_plan.h")
 
 
 def kernel_source_sha1():
@@ -869,13 +869,13 @@ def main():
     def roof(kernel, nbytes, ms, tkey):
         ach = nbytes / (ms * 1e-3) / 1e9
         # the record's keys are the profiler's kernel names, arguments included
-        t = next((v for k, v in (traffic or {}).items() if k.startswith(tkey)), None)
+        t = sum(v for k, v in (traffic or {}).items() if k.startswith(tkey)) or None
         return dict(bound="hbm", achieved=round(ach, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                     frac=round(ach / HBM_PEAK_GBS, 4), traffic=t, kernel=kernel,
                     bytes_per_launch=int(nbytes), avg_ms=round(ms, 4))
 
     r_beam = roof("k_beam", st["bytes_beam"], float(np.mean(beam_ms)), "k_beam<0, 1, 8>")
-    r_greedy = (roof("k_greedy", st["bytes_greedy"], float(np.mean(gk_ms)), "k_greedy<0, 1, 8>")
+    r_greedy = (roof("k_greedy", st["bytes_greedy"], float(np.mean(gk_ms)), ("k_greedy<0, 1, 8>", "k_greedy_local<0, 1, 8>"))
                 if st["greedy_kernel_ms"] > 0 else None)
     dominant = r_greedy if r_greedy and r_greedy["avg_ms"] > r_beam["avg_ms"] else r_beam
     log(f"adaptive b={A['beam']}: {qps:,.0f} QPS; beam kernel {r_beam['avg_ms']:.3f} ms "

@@ -290,7 +290,10 @@ rr_status rr_range_search_noalloc(const rr_index *idx, const void *queries_dev, 
                                   rr_query_stats *stats_dev, void *stream);
 
 /* Exact range search by a dense scan (Definition 2.1), for ground truth.
- * Same arguments and result layout as rr_range_search. */
+ * Same arguments and result layout as rr_range_search.  On float32 data the
+ * scans (this one and rr_nn_dist) take device scratch of about 4 bytes per
+ * value of the padded queries for a filter on the matrix cores; where the
+ * allocator has no room for it they run in FP64 alone. */
 rr_status rr_brute_force(const rr_index *idx, const void *queries_dev, int64_t nq,
                          double radius, const double *radius_dev, const rr_allocator *alloc,
                          void *stream, rr_results **out);

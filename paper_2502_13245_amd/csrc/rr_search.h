@@ -2426,6 +2426,8 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
     O *const idist = (O *)a.sb.item_dist;
     O *const sc = (O *)a.sb.seg_dists + (int64_t)blockIdx.x * cap; // the list's distances
     unsigned long long *const queue = &a.sb.counters[CTR_LOCAL_QUEUE];
+    // tickets given out when few enough workgroups are busy
+    const int64_t idle = ntasks + (int64_t)gridDim.x - a.busy.low, idle_long = ntasks + (int64_t)gridDim.x - a.busy.high;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.sb.level_clock[LOCAL_CLOCK] = wall_clock64();
 
     for (;;) {
@@ -2499,11 +2501,9 @@ __global__ __launch_bounds__((local_waves<DTYPE, CPL>() * 64)) void k_greedy_loc
                 if (p == RR_EMPTY32) break;
                 // now and then: how many workgroups are busy?  (the others have
                 // taken one ticket past the end each)
-                const int backlog = *v_tail - k0;
-                if ((k0 & 31) == 0 && backlog > LOCAL_BACKLOG) {
+                if ((k0 & 31) == 0 && *v_tail - k0 > LOCAL_BACKLOG) {
                     const int64_t given = (int64_t)__hip_atomic_load(queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const int64_t busy = gridDim.x - max((int64_t)0, given - ntasks);
-                    if (busy <= (backlog > LOCAL_WAIT ? a.busy.high : a.busy.low) && lane == 0) *v_stop = 1;
+                    if (given >= (*v_tail - k0 > LOCAL_WAIT ? idle_long : idle) && lane == 0) *v_stop = 1;
                 }
             }
             const int32_t f = np == p ? nf : row(p);
